@@ -25,7 +25,6 @@ static __device__ __align__(256) unsigned char scratch[BLINK_NOALLOC_SCRATCH_BYT
 
 namespace {
 
-constexpr int SORT_RUN_SMALL = 1024;
 constexpr int SORT_RUN = 8192;
 constexpr int MAX_GRID_Y = 65535;
 constexpr size_t CHUNK_TARGET_BYTES = size_t(1) << 30;    // half-spectrum bytes per chunk
@@ -303,11 +302,35 @@ struct Timer {
 constexpr int SORTED_VMAX = 1;     // the per-timestep largest |v|
 constexpr int SORTED_BOUNDS = 2;   // the cell bounds of every image (one channel per timestep)
 
-// per-timestep order of the usable baselines by u (metres). With `img` (the
-// image call), the small-list sort also writes the per-timestep largest |v|
-// and, when there is one channel per timestep, the images' cell bounds.
+// One-launch sort. Workgroups that share a timestep each repeat the load and
+// the bucket counts and order their part of the list, so more of them pay only
+// while the chip has idle CUs: up to eight, and at most one wave of 256 in all.
+// A list longer than SORT_SHARE is ordered in at least four parts, so that a
+// part of an uneven list still fits in LDS.
+// Many long lists at once leave the gathers to k_sort_gather.
+inline bool sort_split(int B, int nt) { return B > 8 * 1024 && nt > 32; }
+
+template <int THREADS, int PER>
+void launch_sort(const SortArgs& s, int nt, bool bounds, hipStream_t st) {
+  const int groups = s.B <= 1024 ? 1 : std::max(1, std::min(8, 256 / nt));
+  const int shares = s.B > SORT_SHARE ? std::max(4, groups) : groups;
+  const dim3 g(groups, nt), wg(THREADS);
+  const size_t lds = SortWg<THREADS>::lds_bytes(s.B);
+  const bool split = sort_split(s.B, nt);
+  if (bounds) hipLaunchKernelGGL((k_sort_one<THREADS, PER, true>), g, wg, lds, st, s, shares, 0);
+  else hipLaunchKernelGGL((k_sort_one<THREADS, PER, false>), g, wg, lds, st, s, shares, split ? 1 : 0);
+  if (split) {
+    const int blocks = (int)cdiv(s.B, 256);
+    hipLaunchKernelGGL(k_sort_gather, dim3((unsigned)(cdiv(nt, 8) * 8 * blocks)), dim3(256), 0, st, s, nt, blocks);
+  }
+}
+
+// per-timestep order of the usable baselines by u (metres). Lists of up to
+// SORT_ONE baselines take one launch, which also writes the per-timestep
+// largest |v| and, when there is one channel per timestep, the images' cell
+// bounds.
 int run_sort(const blink_problem* p, const blink_inputs* in, const Work& w, hipStream_t st,
-             Timer* tm = nullptr, bool img = false) {
+             Timer* tm = nullptr) {
   Timer none;
   Timer& T_ = tm ? *tm : none;
   const int T = p->n_time, B = p->n_bl;
@@ -338,9 +361,9 @@ int run_sort(const blink_problem* p, const blink_inputs* in, const Work& w, hipS
     s.eu[0] = n0 + m0 * m0 * k; s.eu[1] = -l0 * m0 * k; s.eu[2] = -l0;
     s.ev[0] = -l0 * m0 * k; s.ev[1] = n0 + l0 * l0 * k; s.ev[2] = -m0;
   }
-  const bool small = B > 0 && B <= SORT_RUN;
-  const bool bounds = img && small && p->n_chan == 1;
-  if (img && small) s.vmax = w.vmax;
+  const bool one = B > 0 && B <= SORT_ONE;
+  const bool bounds = one && p->n_chan == 1 && !sort_split(B, T);
+  if (one) s.vmax = w.vmax;
   if (bounds) {
     s.N = p->grid_n;
     s.kw = p->kernel_support;
@@ -349,7 +372,7 @@ int run_sort(const blink_problem* p, const blink_inputs* in, const Work& w, hipS
     s.bnd = w.bnd;
     s.ncz = w.ncz;
   }
-  if (B == 0 || B > SORT_RUN) {
+  if (!one) {
     T_.begin(0);
     hipLaunchKernelGGL(k_sort_init, dim3(cdiv(2LL * T, 256)), dim3(256), 0, st, w.counters, 2 * T);
     T_.end();
@@ -359,15 +382,10 @@ int run_sort(const blink_problem* p, const blink_inputs* in, const Work& w, hipS
     const int nt = std::min(MAX_GRID_Y, T - t0);
     s.t0 = t0;
     T_.begin(0);
-    if (B <= SORT_RUN_SMALL) {
-      if (bounds) hipLaunchKernelGGL((k_sort_small<SORT_RUN_SMALL, true>), dim3(1, nt), dim3(1024), 0, st, s);
-      else hipLaunchKernelGGL((k_sort_small<SORT_RUN_SMALL>), dim3(1, nt), dim3(1024), 0, st, s);
-      T_.end();
-      continue;
-    }
-    if (B <= SORT_RUN) {
-      if (bounds) hipLaunchKernelGGL((k_sort_small<SORT_RUN, true>), dim3(1, nt), dim3(1024), 0, st, s);
-      else hipLaunchKernelGGL((k_sort_small<SORT_RUN>), dim3(1, nt), dim3(1024), 0, st, s);
+    if (one) {
+      if (B <= 4 * 256) launch_sort<256, 4>(s, nt, bounds, st);
+      else if (B <= 8 * 1024) launch_sort<1024, 8>(s, nt, bounds, st);
+      else launch_sort<1024, 32>(s, nt, bounds, st);
       T_.end();
       continue;
     }
@@ -384,7 +402,16 @@ int run_sort(const blink_problem* p, const blink_inputs* in, const Work& w, hipS
     hipLaunchKernelGGL(k_sort_finish, dim3(cdiv(B, 256), nt), dim3(256), 0, st, s, src);
     T_.end();
   }
-  return small && img ? (SORTED_VMAX | (bounds ? SORTED_BOUNDS : 0)) : 0;
+  return one ? ((w.vmax ? SORTED_VMAX : 0) | (bounds ? SORTED_BOUNDS : 0)) : 0;
+}
+
+// Cell bounds of every image. A list is scanned in segments of about 2,048
+// entries, or searched for 256 bounds a workgroup when it is much longer than
+// the bounds (see k_bounds).
+void run_bounds(const ImgArgs& a, long long n_img, hipStream_t st) {
+  long long segs = a.B > 16 * (a.N + 2) ? cdiv(a.N + 2, BND_THREADS) : cdiv(a.B, 2048);
+  segs = std::max(1LL, std::min(segs, ((1LL << 24) - 1) / n_img));
+  hipLaunchKernelGGL(k_bounds, dim3((unsigned)(n_img * segs)), dim3(BND_THREADS), 0, st, a, (int)segs);
 }
 
 ImgArgs make_args(const blink_problem* p, const blink_inputs* in, const Work& w) {
@@ -540,7 +567,7 @@ blink_status image_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t s
   a.wtiles = cols_half<N>() && !kb ? N / 2 : (int)cdiv(N / 2, cpw);
   if (!(sorted & SORTED_BOUNDS)) {
     T_.begin(1);
-    hipLaunchKernelGGL(k_bounds, dim3((unsigned)n_img), dim3(256), 0, st, a);
+    run_bounds(a, n_img, st);
     T_.end();
   }
   for (long long i0 = 0; i0 < n_img; i0 += chunk) {
@@ -581,12 +608,12 @@ blink_status image_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t s
 }
 
 template <int N>
-blink_status grid_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t st) {
+blink_status grid_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t st, int sorted) {
   const long long n_img = (long long)p->n_time * p->n_chan;
   const bool uni = p->weighting == BLINK_UNIFORM;
   const size_t lds1 = Cols<N>::grid_lds_bytes(true);
   a.wtiles = (int)cdiv(N, Cols<N>::CPW);
-  hipLaunchKernelGGL(k_bounds, dim3((unsigned)n_img), dim3(256), 0, st, a);
+  if (!(sorted & SORTED_BOUNDS)) run_bounds(a, n_img, st);
   for (long long i0 = 0; i0 < n_img; i0 += chunk) {
     const int n = (int)std::min<long long>(chunk, n_img - i0);
     a.img0 = (int)i0; a.nimg = n;
@@ -610,14 +637,14 @@ blink_status grid_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t st
 }
 
 template <int N>
-blink_status adjoint_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t st) {
+blink_status adjoint_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t st, int sorted) {
   const long long n_img = (long long)p->n_time * p->n_chan;
   const bool uni = p->weighting == BLINK_UNIFORM;
   const bool kb = p->kernel_support > 0;
   if (a.gains)
     hipLaunchKernelGGL(k_fill2, dim3(cdiv(a.B, 256)), dim3(256), 0, st, a.pacc, (size_t)a.B);
   a.wtiles = (int)cdiv(N / 2, Cols<N>::CPW);
-  hipLaunchKernelGGL(k_bounds, dim3((unsigned)n_img), dim3(256), 0, st, a);
+  if (!(sorted & SORTED_BOUNDS)) run_bounds(a, n_img, st);
   for (long long i0 = 0; i0 < n_img; i0 += chunk) {
     const int n = (int)std::min<long long>(chunk, n_img - i0);
     a.img0 = (int)i0; a.nimg = n;
@@ -755,13 +782,13 @@ blink_status blink_grid(const blink_problem* p, const blink_inputs* in, blink_c3
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   Work w{};
   carve(p, BLINK_CALL_GRID, chunk, static_cast<char*>(workspace), &w);
-  run_sort(p, in, w, st);
+  const int sorted = run_sort(p, in, w, st);
   ImgArgs a = make_args(p, in, w);
   a.grid = reinterpret_cast<float2*>(grid);
   a.counts = counts;
   a.weight_sum = weight_sum;
   a.n_dropped = n_dropped;
-#define BLINK_GRID_CALL(n) grid_n<n>(p, a, chunk, st)
+#define BLINK_GRID_CALL(n) grid_n<n>(p, a, chunk, st, sorted)
   BLINK_DISPATCH_N(p->grid_n, BLINK_GRID_CALL)
 #undef BLINK_GRID_CALL
 }
@@ -796,7 +823,7 @@ static blink_status image_batch_impl(const blink_problem* p, const blink_inputs*
   tm->st = st;
   Work w{};
   carve(p, BLINK_CALL_IMAGE, chunk, static_cast<char*>(workspace), &w);
-  const int sorted = run_sort(p, in, w, st, tm, true);
+  const int sorted = run_sort(p, in, w, st, tm);
   if (p->n_bl > 0 && !(sorted & SORTED_VMAX)) {
     tm->begin(0);
     hipLaunchKernelGGL(k_vmax, dim3((unsigned)p->n_time), dim3(256), 0, st, w.sv, w.counters + p->n_time,
@@ -945,13 +972,13 @@ blink_status blink_degrid_adjoint(const blink_problem* p, const blink_inputs* in
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   Work w{};
   carve(p, BLINK_CALL_ADJOINT, chunk, static_cast<char*>(workspace), &w);
-  run_sort(p, in, w, st);
+  const int sorted = run_sort(p, in, w, st);
   ImgArgs a = make_args(p, in, w);
   a.image_grad = image_grad;
   a.wsum_in = weight_sum;
   a.vis_grad = reinterpret_cast<float2*>(vis_grad);
   a.gain_grad = reinterpret_cast<float2*>(gain_grad);
-#define BLINK_ADJ_CALL(n) adjoint_n<n>(p, a, chunk, st)
+#define BLINK_ADJ_CALL(n) adjoint_n<n>(p, a, chunk, st, sorted)
   BLINK_DISPATCH_N(p->grid_n, BLINK_ADJ_CALL)
 #undef BLINK_ADJ_CALL
 }

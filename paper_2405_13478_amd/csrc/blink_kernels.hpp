@@ -1,8 +1,9 @@
 // HIP kernels of the dirty-imaging path for gfx950.
 //
 // Per timestep t (shared by all channels):
-//   k_sort_run / k_merge / k_sort_finish - order the usable baselines by u in
-//       metres (exact double comparison, ties by baseline index). Because
+//   k_sort_one (lists above SORT_ONE: k_sort_run / k_merge / k_sort_finish) -
+//       order the usable baselines by u in metres (exact double comparison, ties
+//       by baseline index). Because
 //       rint(u * s_c) is non-decreasing in u for every s_c > 0, the baselines of
 //       one u cell form a contiguous run of this order at EVERY channel, so one
 //       sort serves all channels of the timestep.
@@ -48,6 +49,11 @@ __device__ __forceinline__ unsigned long long order_key(double u) {
   return (b >> 63) ? ~b : (b | (1ull << 63));
 }
 
+// The double that order_key maps to a key.
+__device__ __forceinline__ double key_value(unsigned long long k) {
+  return __longlong_as_double((long long)((k >> 63) ? k & ~(1ull << 63) : ~k));
+}
+
 // ============================================================== sort by u
 struct SortArgs {
   int T, B;
@@ -71,7 +77,7 @@ struct SortArgs {
   int n_ant;                     // cable length entries; an antenna index outside [0, n_ant) adds 0
   double* vmax;                  // [T] largest |v| of the usable baselines, or null
   // single-image bounds (one channel per timestep): the cell bounds of image t
-  // are formed by the sort kernel itself (see k_sort_small)
+  // are formed by the sort kernel itself (see k_sort_one)
   int N, kw;                     // grid size, gridding kernel support (0: nearest cell)
   double ndx;                    // fl(N * dx)
   const double* freq;            // [1]
@@ -173,121 +179,530 @@ __global__ void __launch_bounds__(1024) k_sort_run(SortArgs a) {
   if (threadIdx.x == 0 && s_unf) atomicAdd(&a.n_unflagged[t], s_unf);
 }
 
-// Cell bounds of one image from its sorted u (see k_bounds, which documents
-// them): ucol(j) is the clamped u cell of sorted position j. Run by one
-// workgroup; returns nothing, writes bnd[0 .. N + 1] and *ncz.
-template <class UCol>
-__device__ __forceinline__ void image_bounds(UCol&& ucol, int nv, int N, int kw, int* bnd, int* ncz) {
-  const int H = N / 2;
-  const int clast = nv == 0 ? -H - 1 : ucol(nv - 1);
-  if (nv > 16 * (N + 2)) {
-    for (int c = (int)threadIdx.x - H; c <= H + 1; c += blockDim.x) {
-      int lo = 0, hi = nv;
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (ucol(mid) >= c) hi = mid; else lo = mid + 1;
-      }
-      bnd[c + H] = lo;
-    }
-  } else {
-    for (int j = threadIdx.x; j < nv; j += blockDim.x) {
-      const int cj = ucol(j);
-      const int cp = j == 0 ? -H - 1 : ucol(j - 1);
-      for (int c = cp + 1; c <= cj; ++c) bnd[c + H] = j;
-    }
-    for (int c = clast + 1 + (int)threadIdx.x; c <= H + 1; c += blockDim.x) bnd[c + H] = nv;
-  }
-  // every entry lies in a column |c| <= max(|first|, |last|) of the sorted order;
-  // a gridding kernel reaches columns c with |c - x_u| <= W/2, i.e. at most
-  // floor(W/2 + 1/2) columns beyond the entry's nearest one
+// Half-spectrum columns that may hold data, given the clamped u cells of the
+// first and the last of nv sorted entries: every entry lies in a column
+// |c| <= max(|first|, |last|), and a gridding kernel reaches columns c with
+// |c - x_u| <= W/2, i.e. at most floor(W/2 + 1/2) columns beyond the entry's
+// nearest one.
+__device__ __forceinline__ int nonempty_columns(int cfirst, int clast, int nv, int N, int kw) {
   const int reach = kw > 0 ? (kw + 1) / 2 : 0;
-  if (threadIdx.x == 0) *ncz = nv == 0 ? 0 : min(H, max(clast, -ucol(0)) + 1 + reach);
+  return nv == 0 ? 0 : min(N / 2, max(clast, -cfirst) + 1 + reach);
 }
 
-// Whole per-timestep order in one kernel when B <= RUN: load, bitonic sort in
-// LDS, then the sorted u, v, baseline index, the two counters and the largest
-// |v| of the timestep (one workgroup per timestep, so no atomics and no
-// initialisation). BOUNDS (one channel per timestep): the same workgroup then
-// forms the cell bounds of its image, which saves the bounds launch.
-template <int RUN, bool BOUNDS = false>
-__global__ void __launch_bounds__(1024) k_sort_small(SortArgs a) {
-  __shared__ unsigned long long sk[RUN];
-  __shared__ int si[RUN];
-  __shared__ int s_unf, s_val;
-  __shared__ double s_vm[1024 / WAVE];
-  const int t = a.t0 + blockIdx.y;
-  const size_t tb = (size_t)t * a.B;
-  if (threadIdx.x == 0) { s_unf = 0; s_val = 0; }
+// ------------------------------------------------ order of one timestep in one launch
+// The order of up to SORT_ONE baselines of a timestep, (key, index) ascending
+// with the key order_key(u), by one bucket pass instead of a comparison network
+// (91 passes with a barrier each for 8,192 keys):
+//   1. every thread loads its PER baselines (u, v, flag); a block reduction
+//      finds the range of the usable u, their number and the largest |v|;
+//   2. u is mapped linearly onto nb buckets. Subtraction, product and
+//      truncation never decrease with u, so the buckets are in order of u.
+//      Their counts are LDS integer atomics (two 16-bit counts a word), and the
+//      count returned is the baseline's slot in its bucket;
+//   3. a scan gives each bucket its first sorted position;
+//   4. the keys and indices go to their buckets in LDS;
+//   5. an entry's position is its bucket's start plus the number of smaller
+//      (key, index) pairs in the bucket (about one entry a bucket when u is
+//      spread evenly; a centrally condensed array fills some with ten). Buckets
+//      above SORT_LIGHT entries are sorted in place by a wavefront each, or by
+//      the whole workgroup;
+//   6. u, v, index and delay are written in order (index_only: the index
+//      alone, see k_sort_gather).
+// The positions are taken in `shares` parts, whole buckets each: as many as
+// fit in LDS, walked by one workgroup per timestep, or by gridDim.x of them
+// that each repeat 1-3.
+// A share that does not fit in LDS (a long list with most of it in one bucket)
+// is ordered by a stable radix sort of the keys instead, four bits a pass,
+// skipping digits that all keys share.
+// What bounds it: the latency of one workgroup (loads, barriers, LDS atomics),
+// not bandwidth; with many long lists the reads of uvw. Measured against the
+// networks and merges before it (whole order, largest |v| included): 496
+// baselines 24 -> 8 us, 8,128 baselines 130 -> 15 us, 32,640 baselines 185 ->
+// 45 us for one timestep and 900 -> 273 us for 200.
+constexpr int SORT_ONE = 32768;          // largest list of this kernel (16-bit positions)
+constexpr int SORT_LIGHT = 128;          // larger buckets are sorted, not ranked by counting
+constexpr int SORT_WAVE_MAX = 2048;      // larger ones by the whole workgroup
+constexpr int SORT_SHARE = 10752;        // entries of a share that fit in LDS beside the bucket starts
+constexpr int SORT_RADIX = 16;           // digits of the radix passes
+
+// Workgroup shapes: lists of up to 2,048 baselines take 256 threads (eight such
+// workgroups share a CU), longer ones 1,024.
+template <int THREADS>
+struct SortWg {
+  // buckets for a list of n baselines: about one a baseline, from two a thread on
+  __host__ __device__ static constexpr int buckets(int n) {
+    int nb = 2 * THREADS;
+    while (nb < n && nb < 16384) nb *= 2;
+    return nb;
+  }
+  __host__ __device__ static constexpr int share(int n) { return n < SORT_SHARE ? n : SORT_SHARE; }
+  // keys, indices and order of a share; or permutation and digit counts of the radix passes
+  __host__ __device__ static constexpr size_t list_bytes(int n) {
+    const size_t list = (size_t)((share(n) + 7) & ~7) * 12;
+    const size_t radix = (size_t)((n + 7) & ~7) * 2 + (size_t)SORT_RADIX * THREADS * 2;
+    return n > SORT_SHARE && radix > list ? radix : list;
+  }
+  __host__ __device__ static constexpr size_t lds_bytes(int n) {
+    return list_bytes(n) + (size_t)(buckets(n) / 2 + 1) * 4;
+  }
+};
+
+// Exclusive scan of one value per thread over the workgroup; `tot` is one word
+// a wavefront that nothing else uses between the barriers.
+template <int THREADS>
+__device__ __forceinline__ unsigned block_exclusive(unsigned v, unsigned* tot) {
+  const int lane = threadIdx.x % WAVE, wave = threadIdx.x / WAVE;
+  unsigned s = v;
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const unsigned x = __shfl_up(s, o);
+    if (lane >= o) s += x;
+  }
+  if (lane == WAVE - 1) tot[wave] = s;
   __syncthreads();
-  int unf = 0, val = 0;
-  for (int i = threadIdx.x; i < RUN; i += blockDim.x) {
-    unsigned long long k = KEY_MAX;
-    int id = 0x7fffffff;
-    if (i < a.B) {
-      double u, v;
-      plane_uv(a, tb + i, u, v);
+  unsigned base = 0;
+#pragma unroll
+  for (int w = 0; w < THREADS / WAVE; ++w) base += w < wave ? tot[w] : 0u;
+  return base + s - v;
+}
+
+// The key of baseline i: usable ones by u, flagged and non-finite ones last.
+__device__ __forceinline__ unsigned long long baseline_key(const SortArgs& a, size_t tb, int i) {
+  double u, v;
+  plane_uv(a, tb + i, u, v);
+  const bool flagged = a.flags != nullptr && a.flags[tb + i] != 0;
+  return !flagged && isfinite(u) && isfinite(v) ? order_key(u) : KEY_MAX;
+}
+
+// In-place sort of n (key, index) pairs in LDS by `width` threads (rank r of
+// them): a bitonic network whose comparators all point the same way (each
+// merge starts by comparing mirrored positions), so that it ends at any n.
+template <class Sync>
+__device__ __forceinline__ void sort_pairs(unsigned long long* key, unsigned short* id, int n, int r, int width,
+                                           Sync&& sync) {
+  auto exchange = [&](int x, int y) {
+    if (y >= n) return;
+    const unsigned long long kx = key[x], ky = key[y];
+    const unsigned short ix = id[x], iy = id[y];
+    if (kx > ky || (kx == ky && ix > iy)) {
+      key[x] = ky; key[y] = kx;
+      id[x] = iy; id[y] = ix;
+    }
+  };
+  for (int k = 2; k / 2 < n; k <<= 1) {
+    for (int p = r; p < (n + k - 1) / k * (k / 2); p += width) {
+      const int base = p / (k / 2) * k, q = p % (k / 2);
+      exchange(base + q, base + k - 1 - q);
+    }
+    sync();
+    for (int j = k >> 2; j > 0; j >>= 1) {
+      for (int p = r; p < (n + 2 * j - 1) / (2 * j) * j; p += width) {
+        const int x = 2 * p - (p & (j - 1));
+        exchange(x, x + j);
+      }
+      sync();
+    }
+  }
+}
+
+// Stable radix order of all B keys of the timestep into perm (16-bit indices,
+// LDS); cnt: SORT_RADIX x THREADS 16-bit counts (LDS). Thread t owns the
+// positions [t per, (t + 1) per), so counts in thread order keep it stable.
+template <int THREADS, int PER>
+__device__ __forceinline__ void radix_order(const SortArgs& a, size_t tb, unsigned short* perm, unsigned short* cnt,
+                                            unsigned* tot, unsigned long long* s_diff) {
+  const int tid = threadIdx.x, B = a.B;
+  const int per = (B + THREADS - 1) / THREADS;                       // <= PER
+  __syncthreads();
+  if (tid == 0) *s_diff = 0ull;
+  __syncthreads();
+  const unsigned long long k0 = baseline_key(a, tb, 0);
+  unsigned long long diff = 0ull;
+  for (int i = tid; i < B; i += THREADS) {
+    diff |= baseline_key(a, tb, i) ^ k0;
+    perm[i] = (unsigned short)i;
+  }
+  for (int o = WAVE / 2; o > 0; o >>= 1) diff |= __shfl_xor(diff, o);
+  if (tid % WAVE == 0 && diff != 0ull) atomicOr(s_diff, diff);
+  __syncthreads();
+  diff = *s_diff;
+  for (int sh = 0; sh < 64; sh += 4) {
+    if (((diff >> sh) & (SORT_RADIX - 1)) == 0ull) continue;         // one digit for all: no change
+    for (int d = 0; d < SORT_RADIX; ++d) cnt[d * THREADS + tid] = 0;
+    unsigned short id[PER];
+    unsigned char dg[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int j = tid * per + k;
+      if (k < per && j < B) {
+        id[k] = perm[j];
+        dg[k] = (unsigned char)((baseline_key(a, tb, id[k]) >> sh) & (SORT_RADIX - 1));
+        ++cnt[dg[k] * THREADS + tid];
+      }
+      if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);             // bounds the loads in flight
+    }
+    __syncthreads();
+    // exclusive scan in (digit, thread) order: SORT_RADIX consecutive counts a thread
+    unsigned sum = 0;
+    for (int e = 0; e < SORT_RADIX; ++e) sum += cnt[tid * SORT_RADIX + e];
+    unsigned at = block_exclusive<THREADS>(sum, tot);
+    for (int e = 0; e < SORT_RADIX; ++e) {
+      const unsigned c = cnt[tid * SORT_RADIX + e];
+      cnt[tid * SORT_RADIX + e] = (unsigned short)at;
+      at += c;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int j = tid * per + k;
+      if (k < per && j < B) perm[cnt[dg[k] * THREADS + tid]++] = id[k];
+    }
+    __syncthreads();
+  }
+}
+
+template <int THREADS, int PER, bool BOUNDS>
+__global__ void __launch_bounds__(THREADS) k_sort_one(SortArgs a, int shares, int index_only) {
+  static_assert(PER <= 32, "one bit a baseline in okm");
+  using W_ = SortWg<THREADS>;
+  constexpr int WAVES = THREADS / WAVE;
+  constexpr int MAX_HEAVY = SORT_SHARE / SORT_LIGHT + 1;
+  extern __shared__ float4 lds_raw[];
+  __shared__ double s_red[3][WAVES];
+  __shared__ int s_cnt[2][WAVES];
+  __shared__ unsigned s_tot[WAVES];
+  __shared__ int s_p0, s_p1, s_ps, s_heavy;
+  __shared__ unsigned s_big;
+  __shared__ unsigned s_list[MAX_HEAVY];             // heavy buckets: start << 16 | size
+  __shared__ unsigned long long s_diff;
+  const int t = a.t0 + blockIdx.y, g = blockIdx.x, G = gridDim.x;
+  const int tid = threadIdx.x, lane = tid % WAVE, wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+  const int B = a.B;
+  const size_t tb = (size_t)t * B;
+  const int cap = (W_::share(B) + 7) & ~7;
+  unsigned long long* keys = reinterpret_cast<unsigned long long*>(lds_raw);
+  unsigned short* ids = reinterpret_cast<unsigned short*>(keys + cap);
+  unsigned short* ord = ids + cap;
+  unsigned* hist = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds_raw) + W_::list_bytes(B));
+  const int nb = W_::buckets(B), wpt = nb / 2 / THREADS;             // buckets; words of two counts a thread
+
+  // 1. load and reduce. Up to 8 baselines a thread stay in registers; of 32
+  // they would spill, so u is read again: from uvw, or (index_only, where su is
+  // not yet written) from a packed copy in su.
+  constexpr bool KEEP = PER <= 8;
+  double u[KEEP ? PER : 1];
+  unsigned okm = 0;
+  double umin = __builtin_inf(), umax = -__builtin_inf(), vm = 0.0;
+  int unf = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {
+    int i = k * THREADS + tid;
+    asm volatile("" : "+v"(i));                                      // its address is formed here, not kept
+    double uk = 0.0;
+    if (i < B) {
+      double v;
+      plane_uv(a, tb + i, uk, v);
       const bool flagged = a.flags != nullptr && a.flags[tb + i] != 0;
       unf += flagged ? 0 : 1;
-      if (!flagged && isfinite(u) && isfinite(v)) { k = order_key(u); ++val; }
-      id = i;
+      if (!flagged && isfinite(uk) && isfinite(v)) {
+        okm |= 1u << k;
+        umin = fmin(umin, uk);
+        umax = fmax(umax, uk);
+        vm = fmax(vm, fabs(v));
+      }
+      if (!KEEP && index_only) a.su[tb + i] = uk;
     }
-    sk[i] = k;
-    si[i] = id;
+    if constexpr (KEEP) u[k] = uk;
+    if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);               // loads in flight
   }
-  if (unf) atomicAdd(&s_unf, unf);
-  if (val) atomicAdd(&s_val, val);
+  auto u_of = [&](int k, int i) -> double {                          // u of baseline i, the thread's k-th
+    if constexpr (KEEP) return u[k];
+    asm volatile("" : "+v"(i));
+    double uk = 0.0, vk;
+    if (i < B) {
+      if (index_only) uk = a.su[tb + i];
+      else plane_uv(a, tb + i, uk, vk);
+    }
+    return uk;
+  };
+  for (int w = tid; w <= nb / 2; w += THREADS) hist[w] = 0u;
+  int val = __popc(okm);
+  for (int o = WAVE / 2; o > 0; o >>= 1) {
+    umin = fmin(umin, __shfl_xor(umin, o));
+    umax = fmax(umax, __shfl_xor(umax, o));
+    vm = fmax(vm, __shfl_xor(vm, o));
+    unf += __shfl_xor(unf, o);
+    val += __shfl_xor(val, o);
+  }
+  if (lane == 0) {
+    s_red[0][wave] = umin; s_red[1][wave] = umax; s_red[2][wave] = vm;
+    s_cnt[0][wave] = unf; s_cnt[1][wave] = val;
+  }
+  if (tid == 0) s_big = 0u;
   __syncthreads();
-  for (int k = 2; k <= RUN; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = threadIdx.x; i < RUN / 2; i += blockDim.x) {
-        const int lo = 2 * i - (i & (j - 1));
-        const int hi = lo + j;
-        const bool up = (lo & k) == 0;
-        const unsigned long long ka = sk[lo], kb = sk[hi];
-        const int ia = si[lo], ib = si[hi];
-        const bool gt = ka > kb || (ka == kb && ia > ib);
-        if (gt == up) {
-          sk[lo] = kb; sk[hi] = ka;
-          si[lo] = ib; si[hi] = ia;
+  {
+    const int w = lane % WAVES;
+    umin = s_red[0][w]; umax = s_red[1][w]; vm = s_red[2][w];
+    unf = s_cnt[0][w]; val = s_cnt[1][w];
+    for (int o = WAVES / 2; o > 0; o >>= 1) {
+      umin = fmin(umin, __shfl_xor(umin, o));
+      umax = fmax(umax, __shfl_xor(umax, o));
+      vm = fmax(vm, __shfl_xor(vm, o));
+      unf += __shfl_xor(unf, o);
+      val += __shfl_xor(val, o);
+    }
+  }
+  const int nv = val;
+  if (g == 0 && tid == 0) {
+    a.n_unflagged[t] = unf;
+    a.n_valid[t] = nv;
+    if (a.vmax != nullptr) a.vmax[t] = vm;
+  }
+
+  // 2. buckets and slots (a degenerate range puts all into one bucket)
+  double scale = (double)nb / (umax - umin);
+  if (!(umax > umin) || !isfinite(scale)) scale = 0.0;
+  auto bucket_of = [&](double x) -> unsigned {                        // (unusable ones: any bucket)
+    return (unsigned)fmin(fmax((x - umin) * scale, 0.0), (double)(nb - 1));
+  };
+  unsigned bs[PER];                                                  // bucket and slot << 16
+  constexpr int BATCH = PER < 8 ? PER : 8;                            // LDS round trips in flight
+#pragma unroll
+  for (int k0 = 0; k0 < PER; k0 += BATCH) {
+    unsigned old[BATCH];
+    double uk[BATCH];
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e) uk[e] = u_of(k0 + e, (k0 + e) * THREADS + tid);
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e) {
+      const int k = k0 + e;
+      bs[k] = bucket_of(uk[e]);
+      old[e] = 0u;
+      if ((okm >> k) & 1u) old[e] = atomicAdd(&hist[bs[k] >> 1], 1u << ((bs[k] & 1u) * 16u));
+    }
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e)
+      bs[k0 + e] |= ((old[e] >> ((bs[k0 + e] & 1u) * 16u)) & 0xffffu) << 16;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  __syncthreads();
+
+  // 3. bucket starts, in place, and the largest bucket
+  {
+    unsigned c[8], sum = 0, big = 0;                                 // counts of up to 16 buckets
+    static_assert(W_::buckets(SORT_ONE) / 2 / THREADS <= 8 || THREADS < 1024, "words of counts a thread");
+    if (wpt % 4 == 0) {                                              // 16 bytes a lane: few bank conflicts
+#pragma unroll
+      for (int w = 0; w < 8; w += 4)
+        if (w < wpt) *reinterpret_cast<uint4*>(c + w) = *reinterpret_cast<const uint4*>(hist + tid * wpt + w);
+    } else {
+      c[0] = hist[tid * wpt];
+      c[1] = wpt > 1 ? hist[tid * wpt + 1] : 0u;
+    }
+#pragma unroll
+    for (int w = 0; w < 8; ++w)
+      if (w < wpt) {
+        sum += (c[w] & 0xffffu) + (c[w] >> 16);
+        big = max(big, max(c[w] & 0xffffu, c[w] >> 16));
+      }
+    for (int o = WAVE / 2; o > 0; o >>= 1) big = max(big, __shfl_xor(big, o));
+    if (lane == 0) atomicMax(&s_big, big);
+    unsigned at = block_exclusive<THREADS>(sum, s_tot);
+#pragma unroll
+    for (int w = 0; w < 8; ++w)
+      if (w < wpt) {
+        const unsigned e0 = at + (c[w] & 0xffffu), e1 = e0 + (c[w] >> 16);
+        c[w] = at | (e0 << 16);
+        at = e1;
+      }
+    if (wpt % 4 == 0) {
+#pragma unroll
+      for (int w = 0; w < 8; w += 4)
+        if (w < wpt) *reinterpret_cast<uint4*>(hist + tid * wpt + w) = *reinterpret_cast<const uint4*>(c + w);
+    } else {
+      hist[tid * wpt] = c[0];
+      if (wpt > 1) hist[tid * wpt + 1] = c[1];
+    }
+    if (tid == THREADS - 1) hist[nb / 2] = at;                       // start of bucket nb: nv
+  }
+  __syncthreads();
+  auto start_of = [&](unsigned b) -> int { return (int)((hist[b >> 1] >> ((b & 1u) * 16u)) & 0xffffu); };
+
+  // 6. the entries at sorted positions [p0, p1), index_at(j) the baseline at
+  // position j (p0 - 1 too, for the bounds)
+  const double s = BOUNDS ? cells_per_metre(a.freq[0], a.ndx) : 0.0;
+  const int H = a.N / 2;
+  auto cell = [&](double x) -> int { return (int)fmin(fmax(rint(x * s), (double)-H), (double)H); };
+  int* bnd = BOUNDS ? a.bnd + (size_t)t * (a.N + 2) : nullptr;
+  auto write = [&](int p0, int p1, auto&& index_at) {
+    constexpr int U = 4;                                             // gathers in flight
+    for (int j0 = p0; j0 < p1; j0 += U * THREADS) {
+      int bi[U];
+      double uj[U], vj[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int j = j0 + k * THREADS + tid;
+        bi[k] = j < p1 ? index_at(j) : 0;
+        uj[k] = vj[k] = 0.0;
+        if (j < p1 && !index_only) plane_uv(a, tb + bi[k], uj[k], vj[k]);
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int j = j0 + k * THREADS + tid;
+        if (j < p1) {
+          a.perm[tb + j] = bi[k];
+          if (!index_only) {
+            a.su[tb + j] = uj[k];
+            a.sv[tb + j] = vj[k];
+            if (a.sd != nullptr) a.sd[tb + j] = baseline_delay(a, tb, bi[k]);
+          }
+        }
+        if constexpr (BOUNDS) {
+          // first sorted position of the cells between the entry before and this one
+          const int cj = cell(uj[k]);
+          int cp = __shfl_up(cj, 1);
+          if (j < p1 && j > 0) {
+            if (lane == 0) {
+              double ul, vl;
+              plane_uv(a, tb + index_at(j - 1), ul, vl);
+              cp = cell(ul);
+            }
+            for (int c = cp + 1; c <= cj; ++c) bnd[c + H] = j;
+          }
         }
       }
-      __syncthreads();
     }
-  }
-  double vm = 0.0;
-  for (int j = threadIdx.x; j < a.B; j += blockDim.x) {
-    const int b = si[j];
-    double u, v;
-    plane_uv(a, tb + b, u, v);
-    a.su[tb + j] = u;
-    a.sv[tb + j] = v;
-    if (a.sd != nullptr) a.sd[tb + j] = baseline_delay(a, tb, b);
-    a.perm[tb + j] = b;
-    if (j < s_val) vm = fmax(vm, fabs(v));        // usable entries sort first
-  }
-  for (int o = WAVE / 2; o > 0; o >>= 1) vm = fmax(vm, __shfl_xor(vm, o));
-  if (threadIdx.x % WAVE == 0) s_vm[threadIdx.x / WAVE] = vm;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    a.n_unflagged[t] = s_unf;
-    a.n_valid[t] = s_val;
-    if (a.vmax != nullptr) {
-      double m = 0.0;
-      for (int w = 0; w < (int)(blockDim.x / WAVE); ++w) m = fmax(m, s_vm[w]);
-      a.vmax[t] = m;
+    if constexpr (BOUNDS) {
+      // cells up to the first entry's, and beyond the last one's
+      if (p0 == 0 && p1 > 0)
+        for (int c = tid - H; c <= cell(umin); c += THREADS) bnd[c + H] = 0;
+      if (p1 == nv && p1 > p0)
+        for (int c = cell(umax) + 1 + tid; c <= H + 1; c += THREADS) bnd[c + H] = nv;
     }
-  }
+  };
   if constexpr (BOUNDS) {
-    const double s = cells_per_metre(a.freq[0], a.ndx);
-    const int H = a.N / 2;
-    auto ucol = [&](int j) -> int {
-      double u, v;
-      plane_uv(a, tb + si[j], u, v);                          // the u of sorted position j
-      const double x = rint(u * s);
-      return (int)fmin(fmax(x, (double)-H), (double)H);
-    };
-    image_bounds(ucol, s_val, a.N, a.kw, a.bnd + (size_t)t * (a.N + 2), a.ncz + t);
+    if (g == 0) {
+      if (tid == 0) a.ncz[t] = nonempty_columns(nv == 0 ? 0 : cell(umin), nv == 0 ? 0 : cell(umax), nv, a.N, a.kw);
+      if (nv == 0)
+        for (int c = tid - H; c <= H + 1; c += THREADS) bnd[c + H] = 0;
+    }
   }
+
+  if (B > SORT_SHARE && (nv + shares - 1) / shares + 2 * (int)s_big > cap) {
+    unsigned short* perm = reinterpret_cast<unsigned short*>(lds_raw);
+    radix_order<THREADS, PER>(a, tb, perm, perm + ((B + 7) & ~7), s_tot, &s_diff);
+    write((int)((long long)nv * g / G), (int)((long long)nv * (g + 1) / G), [&](int j) { return (int)perm[j]; });
+    return;
+  }
+  for (int sh = g; sh < shares; sh += G) {
+    // the share: the buckets after the one that holds position lo - 1, up to
+    // the one that holds hi - 1. The bucket before it (from ps) is kept too, as
+    // the bounds look at the entry before p0: at most a share and two buckets.
+    const int lo = (int)((long long)nv * sh / shares), hi = (int)((long long)nv * (sh + 1) / shares);
+    if (sh != g) __syncthreads();                    // the last share is written
+    if (tid == 0) {
+      s_heavy = 0;
+      if (lo == 0) s_p0 = s_ps = 0;
+      if (hi == 0) s_p1 = 0;
+    }
+    for (int w = tid; w < nb / 2; w += THREADS) {
+      const unsigned h = hist[w];
+      const int st[3] = {(int)(h & 0xffffu), (int)(h >> 16), (int)(hist[w + 1] & 0xffffu)};
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        if (st[e] < lo && lo <= st[e + 1]) { s_ps = st[e]; s_p0 = st[e + 1]; }
+        if (st[e] < hi && hi <= st[e + 1]) s_p1 = st[e + 1];
+      }
+    }
+    __syncthreads();
+    const int p0 = s_p0, p1 = s_p1, ps = s_ps;
+    if (p1 <= p0) continue;
+    // 4. keys and indices to their buckets (what follows from baseline numbers
+    // and okm is formed again: kept from the steps before, it spills)
+    int i4 = tid;
+    asm volatile("" : "+v"(okm), "+v"(i4));
+#pragma unroll
+    for (int k0 = 0; k0 < PER; k0 += BATCH) {
+      int st[BATCH];
+      double uk[BATCH];
+#pragma unroll
+      for (int e = 0; e < BATCH; ++e) {
+        const int k = k0 + e;
+        st[e] = start_of(bs[k] & 0xffffu);
+        st[e] = ((okm >> k) & 1u) && st[e] >= ps && st[e] < p1 ? st[e] - ps + (int)(bs[k] >> 16) : -1;
+        uk[e] = st[e] >= 0 ? u_of(k, k * THREADS + i4) : 0.0;
+      }
+#pragma unroll
+      for (int e = 0; e < BATCH; ++e)
+        if (st[e] >= 0) {
+          keys[st[e]] = order_key(uk[e]);
+          ids[st[e]] = (unsigned short)((k0 + e) * THREADS + i4);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (s_big > (unsigned)SORT_LIGHT)                                // heavy buckets of the share
+      for (int b = tid; b < nb; b += THREADS) {
+        const int st = start_of(b), n = start_of(b + 1u) - st;
+        if (n > SORT_LIGHT && st >= ps && st < p1)
+          s_list[atomicAdd(&s_heavy, 1)] = ((unsigned)(st - ps) << 16) | (unsigned)n;
+      }
+    __syncthreads();
+    const int heavy = s_heavy;
+    if (heavy > 0) {
+      for (int h = wave; h < heavy; h += WAVES) {
+        const int st = (int)(s_list[h] >> 16), n = (int)(s_list[h] & 0xffffu);
+        if (n <= SORT_WAVE_MAX) sort_pairs(keys + st, ids + st, n, lane, WAVE, [] { wave_sync(); });
+      }
+      __syncthreads();
+      for (int h = 0; h < heavy; ++h) {
+        const int st = (int)(s_list[h] >> 16), n = (int)(s_list[h] & 0xffffu);
+        if (n > SORT_WAVE_MAX) sort_pairs(keys + st, ids + st, n, tid, THREADS, [] { __syncthreads(); });
+      }
+    }
+    // 5. rank within the bucket
+    for (int p = tid; p < p1 - ps; p += THREADS) {
+      const unsigned long long key = keys[p];
+      const unsigned b = bucket_of(key_value(key));
+      const int st = start_of(b) - ps, en = start_of(b + 1u) - ps;
+      int at = p;                                                    // heavy buckets are in order already
+      if (en - st <= SORT_LIGHT) {
+        int same = 0;
+        at = st;
+#pragma unroll 4
+        for (int e = st; e < en; ++e) {
+          const unsigned long long ke = keys[e];
+          at += ke < key ? 1 : 0;
+          same += ke == key ? 1 : 0;
+        }
+        if (same > 1) {                                              // equal u: by index
+          const unsigned short id = ids[p];
+          for (int e = st; e < en; ++e) at += keys[e] == key && ids[e] < id ? 1 : 0;
+        }
+      }
+      ord[at] = (unsigned short)p;
+    }
+    __syncthreads();
+    write(p0, p1, [&](int j) { return (int)ids[ord[j - ps]]; });
+  }
+}
+
+// The sorted u, v and delay of the index lists that k_sort_one left, where many
+// long lists are ordered at once: 200 workgroups that gather from lists of 783
+// KB miss their L2s (4 MiB an XCD) on nearly every line, so the gathers go to
+// a launch of their own whose workgroups take the lists of an XCD one after
+// the other (workgroup L runs on XCD L mod 8).
+__global__ void __launch_bounds__(256) k_sort_gather(SortArgs a, int nt, int blocks) {
+  const int L = blockIdx.x, r8 = L >> 3;
+  const int tl = (r8 / blocks) * 8 + (L & 7);
+  if (tl >= nt) return;
+  const int t = a.t0 + tl, j = (r8 % blocks) * 256 + (int)threadIdx.x;
+  if (j >= a.n_valid[t]) return;
+  const size_t tb = (size_t)t * a.B;
+  const int b = a.perm[tb + j];
+  double u, v;
+  plane_uv(a, tb + b, u, v);
+  a.su[tb + j] = u;
+  a.sv[tb + j] = v;
+  if (a.sd != nullptr) a.sd[tb + j] = baseline_delay(a, tb, b);
 }
 
 // Merge neighbouring sorted runs of width w: each element's output position
@@ -397,23 +812,64 @@ struct ImgArgs {
 };
 
 // bnd[c + N/2] = first sorted position j with clamp(rint(u_j s)) >= c for
-// c in [-N/2, N/2 + 1]; entry N + 1 is always n_valid. One workgroup per image.
-// The clamped cell is non-decreasing along the sorted order (s > 0), so each
-// bound is found either by one pass over the list, marking where the cell
-// steps up, or - when the list is much longer than the N + 2 bounds - by a
-// binary search per bound. Both give that first position. For s <= 0 or a
-// non-finite s every bound still lies in [0, n_valid].
-__global__ void __launch_bounds__(256) k_bounds(ImgArgs a) {
-  const int img = blockIdx.x;
+// c in [-N/2, N/2 + 1]; entry N + 1 is always n_valid. The clamped cell is
+// non-decreasing along the sorted order (s > 0), so each bound is found either
+// by one pass over the list, marking where the cell steps up, or - when the
+// list is much longer than the N + 2 bounds - by a binary search per bound.
+// Both give that first position. For s <= 0 or a non-finite s every bound
+// still lies in [0, n_valid].
+// One workgroup per image and segment of the sorted list (`segs` segments an
+// image): a call of few images with long lists is bound by the
+// latency of its longest workgroup, and the segments of a list are independent.
+constexpr int BND_THREADS = 256;
+
+__global__ void __launch_bounds__(BND_THREADS) k_bounds(ImgArgs a, int segs) {
+  const int img = blockIdx.x / segs, seg = blockIdx.x - img * segs;
   const int t = img / a.C, ch = img - t * a.C;
   const double s = cells_per_metre(a.freq[ch], a.ndx);
-  const int H = a.N / 2;
+  const int N = a.N, H = N / 2;
   const double* su = a.su + (size_t)t * a.B;
-  auto ucol = [&](int j) -> int {
-    const double x = rint(su[j] * s);
-    return (int)fmin(fmax(x, (double)-H), (double)H);
-  };
-  image_bounds(ucol, a.n_valid[t], a.N, a.kw, a.bnd + (size_t)img * (a.N + 2), a.ncz + img);
+  const int nv = a.n_valid[t];
+  int* bnd = a.bnd + (size_t)img * (N + 2);
+  auto ucol = [&](int j) -> int { return (int)fmin(fmax(rint(su[j] * s), (double)-H), (double)H); };
+  const int cfirst = nv == 0 ? -H - 1 : ucol(0), clast = nv == 0 ? -H - 1 : ucol(nv - 1);
+  if (seg == 0 && threadIdx.x == 0) a.ncz[img] = nonempty_columns(cfirst, clast, nv, N, a.kw);
+  if (nv > 16 * (N + 2)) {
+    for (int c = (int)threadIdx.x + seg * BND_THREADS - H; c <= H + 1; c += segs * BND_THREADS) {
+      int lo = 0, hi = nv;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (ucol(mid) >= c) hi = mid; else lo = mid + 1;
+      }
+      bnd[c + H] = lo;
+    }
+    return;
+  }
+  const int lane = threadIdx.x % WAVE;
+  const int len = ((a.B + segs - 1) / segs + BND_THREADS - 1) / BND_THREADS * BND_THREADS;
+  const int e = (int)min((long long)nv, (long long)(seg + 1) * len);
+  constexpr int U = 4;                                       // cells in flight per thread
+  for (long long j0 = (long long)seg * len; j0 < e; j0 += U * BND_THREADS) {
+    int cj[U], cp[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const long long j = j0 + k * BND_THREADS + (int)threadIdx.x;
+      cj[k] = j < e ? ucol((int)j) : 0;
+      cp[k] = lane == 0 && j > 0 && j < e ? ucol((int)j - 1) : -H - 1;
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const long long j = j0 + k * BND_THREADS + (int)threadIdx.x;
+      const int up = __shfl_up(cj[k], 1);
+      if (j < e && j > 0)
+        for (int c = (lane == 0 ? cp[k] : up) + 1; c <= cj[k]; ++c) bnd[c + H] = (int)j;
+    }
+  }
+  // the cells up to the first entry's and those beyond the last one's
+  if (seg == 0 && nv > 0)
+    for (int c = (int)threadIdx.x - H; c <= cfirst; c += BND_THREADS) bnd[c + H] = 0;
+  if (seg == segs - 1)
+    for (int c = clast + 1 + (int)threadIdx.x; c <= H + 1; c += BND_THREADS) bnd[c + H] = nv;
 }
 
 // Largest |v| in metres over the usable baselines of each timestep (one
