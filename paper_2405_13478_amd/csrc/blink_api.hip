@@ -727,6 +727,23 @@ blink_status fft2d_n(const float2* in, float2* out, int batch, int sign, hipStre
   return launched();
 }
 
+template <int NBR>
+void launch_xe_rows(const XeArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(k_xengine_all<NBR>, dim3((unsigned)a.nimg), dim3(XeAll<NBR>::THREADS), XeAll<NBR>::LDS, st, a);
+}
+void launch_xe_all(const XeArgs& a, hipStream_t st) {
+  switch ((a.A + 31) / 32) {
+    case 1: return launch_xe_rows<1>(a, st);
+    case 2: return launch_xe_rows<2>(a, st);
+    case 3: return launch_xe_rows<3>(a, st);
+    case 4: return launch_xe_rows<4>(a, st);
+    case 5: return launch_xe_rows<5>(a, st);
+    case 6: return launch_xe_rows<6>(a, st);
+    case 7: return launch_xe_rows<7>(a, st);
+    default: return launch_xe_rows<8>(a, st);
+  }
+}
+
 #define BLINK_DISPATCH_N(n, CALL)                                    \
   switch (n) {                                                       \
     case 8: return CALL(8);                                          \
@@ -1023,17 +1040,38 @@ blink_status blink_correlate(const int8_t* volt, int32_t n_time, int32_t n_chan,
   if (!vis || (n_samp > 0 && !volt)) return BLINK_E_ARG;
   if ((uintptr_t)volt % 16 != 0) return BLINK_E_ARG;
   XeArgs a{};
-  a.volt = volt;
-  a.vis = reinterpret_cast<float2*>(vis);
-  a.autos = autos;
   a.T = n_time; a.C = n_chan; a.A = n_ant; a.S = n_samp;
-  a.nt = (n_ant + XE_TILE - 1) / XE_TILE;
+  const int nt32 = (n_ant + Xe<32>::TILE - 1) / Xe<32>::TILE, nt64 = (n_ant + Xe<64>::TILE - 1) / Xe<64>::TILE;
+  const double tiles32 = 0.5 * nt32 * (nt32 + 1.0);
+  if ((double)((nimg + 7) / 8 * 8) * tiles32 > (double)INT32_MAX) return BLINK_E_SIZE;
+  // One workgroup per spectrum (up to 256 antennas) once there are enough
+  // spectra: 256 antennas x 4096 samples, 512 spectra 390 us against 450 in
+  // large tiles and 571 in small ones, 128 spectra 157 / 125 / 155, 32 spectra
+  // 126 / 87 / 54; 160 antennas x 1024, 100 spectra 22 / 33 / 29; 128 antennas
+  // x 2048, 64 spectra 36 / 46 / 28; 96 antennas x 2048, 64 spectra 22 / 40 /
+  // 25. Else large tiles while they fill the chip, else small ones.
+  const int rows32 = (n_ant + 31) / 32;
+  const bool whole = rows32 <= 8 && nimg >= 20 * rows32;
+  const bool large = nt32 > 1 && (double)nimg * nt64 * (nt64 + 1.0) / 2 >= 256;
+  a.nt = large ? nt64 : nt32;
   a.npairs = a.nt * (a.nt + 1) / 2;
-  a.nimg = nimg;
-  const long long wgs = (nimg + 7) / 8 * 8 * a.npairs;
-  if (wgs > INT32_MAX) return BLINK_E_SIZE;
-  // (n_samp = 0 runs no step and writes zeros)
-  hipLaunchKernelGGL(k_xengine, dim3((unsigned)wgs), dim3(WAVE), 0, reinterpret_cast<hipStream_t>(stream), a);
+  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  // launches of at most 2^32 threads
+  const long long most = whole ? 1LL << 22 : std::max<long long>(8, (1LL << 24) / a.npairs / 8 * 8 - 8);
+  for (long long i = 0; i < nimg; i += most) {
+    a.nimg = std::min(most, nimg - i);
+    a.volt = volt + (size_t)i * n_ant * n_samp * 2;
+    a.vis = reinterpret_cast<float2*>(vis) + (size_t)i * n_ant * (n_ant - 1) / 2;
+    a.autos = autos ? autos + (size_t)i * n_ant : nullptr;
+    if (whole) {
+      launch_xe_all(a, st);
+      continue;
+    }
+    const dim3 g((unsigned)((a.nimg + 7) / 8 * 8 * a.npairs)), wg(XE_THREADS);
+    // (n_samp = 0 runs no step and writes zeros)
+    if (large) hipLaunchKernelGGL(k_xengine<64>, g, wg, Xe<64>::LDS, st, a);
+    else hipLaunchKernelGGL(k_xengine<32>, g, wg, Xe<32>::LDS, st, a);
+  }
   return launched();
 }
 
