@@ -473,16 +473,17 @@ __host__ __device__ constexpr bool plan_even(int n) {
 }
 
 // Twiddle and DFT of the butterflies held in registers (no LDS traffic).
-template <int N, int R, int NS, int SIGN, int ZB = 0, bool CL = false>
+// L: lanes that share a vector (64 / L vectors a wavefront, `lane` within the L).
+template <int N, int R, int NS, int SIGN, int ZB = 0, bool CL = false, int L = WAVE>
 __device__ __forceinline__ void stage_compute(int lane, const float2* __restrict__ tw,
-                                              float2 (&v)[(N / R + WAVE - 1) / WAVE][R]) {
+                                              float2 (&v)[(N / R + L - 1) / L][R]) {
   static_assert(ZB == 0 || NS == 1, "a zero band only on the first stage's inputs");
   constexpr int NB = N / R;
-  constexpr int PER = (NB + WAVE - 1) / WAVE;
+  constexpr int PER = (NB + L - 1) / L;
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int j = lane + p * WAVE;
-    if (NB % WAVE == 0 || j < NB) {
+    const int j = lane + p * L;
+    if (NB % L == 0 || j < NB) {
       if constexpr (NS > 1) {
         constexpr int TW0 = tw_entries_before(N, NS);
         const float2* t1 = tw + TW0 + j % NS;
@@ -509,19 +510,19 @@ __device__ __forceinline__ void stage_compute(int lane, const float2* __restrict
 
 // Round HF of a stage's writes: outputs of the butterflies j in
 // [HF NB/2, (HF + 1) NB/2) to hbuf at padded index - HF pad(N/2).
-template <int N, int R, int NS, int HF>
-__device__ __forceinline__ void half_write(float2* hbuf, int lane, const float2 (&v)[(N / R + WAVE - 1) / WAVE][R]) {
+template <int N, int R, int NS, int HF, int L = WAVE>
+__device__ __forceinline__ void half_write(float2* hbuf, int lane, const float2 (&v)[(N / R + L - 1) / L][R]) {
   constexpr int NB = N / R;
-  constexpr int PER = (NB + WAVE - 1) / WAVE;
+  constexpr int PER = (NB + L - 1) / L;
   constexpr int HB = NB / 2;
   constexpr int PH = pad(N / 2);
   constexpr bool WR_LIN = NS % 16 == 0 || (NS == 1 && 16 % R == 0);
   constexpr int WR_STEP = NS == 1 ? 1 : NS + NS / 16;
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int j = lane + p * WAVE;
+    const int j = lane + p * L;
     bool in;
-    if constexpr (HB % WAVE == 0) in = HF == 0 ? p * WAVE < HB : p * WAVE >= HB;   // whole registers
+    if constexpr (HB % L == 0) in = HF == 0 ? p * L < HB : p * L >= HB;   // whole registers
     else in = HF == 0 ? j < HB : (j >= HB && j < NB);
     if (in) {
       const int base = (j / NS) * NS * R + j % NS;
@@ -540,18 +541,18 @@ __device__ __forceinline__ void half_write(float2* hbuf, int lane, const float2 
 // Round HF of a stage's reads: inputs r in [HF R/2, (HF + 1) R/2), except
 // those in the zero band [R/2 - ZB/2, R/2 + ZB/2) (first stage only), which
 // the codelet treats as zero and which are not read.
-template <int N, int R, int HF, int ZB = 0>
-__device__ __forceinline__ void half_read(const float2* hbuf, int lane, float2 (&v)[(N / R + WAVE - 1) / WAVE][R]) {
+template <int N, int R, int HF, int ZB = 0, int L = WAVE>
+__device__ __forceinline__ void half_read(const float2* hbuf, int lane, float2 (&v)[(N / R + L - 1) / L][R]) {
   constexpr int NB = N / R;
-  constexpr int PER = (NB + WAVE - 1) / WAVE;
+  constexpr int PER = (NB + L - 1) / L;
   constexpr bool RD_LIN = NB % 16 == 0;
   constexpr int RD_STEP = NB + NB / 16;
   constexpr int PH = pad(N / 2);
   constexpr int zlo = R / 2 - ZB / 2, zhi = R / 2 + ZB / 2;
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int j = lane + p * WAVE;
-    if (NB % WAVE == 0 || j < NB) {
+    const int j = lane + p * L;
+    if (NB % L == 0 || j < NB) {
       if constexpr (RD_LIN) {
         const int b = pad(j);
 #pragma unroll
@@ -578,59 +579,57 @@ __host__ __device__ constexpr int zero_band(int n, int bound) {
   return 0;
 }
 
-
-
 // The stages from NS on, given the stage's inputs in v; the last stage hands
 // its outputs to emit(ic<QB>, X) as stockham_last_emit does.
 // ZB: zero band of the first stage's inputs (NS = 1 only; see zero_band).
 // CL: the table is compact in its last stage (tw_entries_compact).
-template <int N, int SIGN, int NS, int ZB = 0, bool CL = false, class Emit>
+template <int N, int SIGN, int NS, int ZB = 0, bool CL = false, int L = WAVE, class Emit>
 __device__ __forceinline__ void half_chain(float2* hbuf, int lane, const float2* __restrict__ tw,
-                                           float2 (&v)[(N / pick_radix(N / NS) + WAVE - 1) / WAVE][pick_radix(N / NS)],
+                                           float2 (&v)[(N / pick_radix(N / NS) + L - 1) / L][pick_radix(N / NS)],
                                            Emit&& emit) {
   constexpr int R = pick_radix(N / NS);
-  constexpr int PER = (N / R + WAVE - 1) / WAVE;
-  stage_compute<N, R, NS, SIGN, ZB, CL>(lane, tw, v);
+  constexpr int PER = (N / R + L - 1) / L;
+  stage_compute<N, R, NS, SIGN, ZB, CL, L>(lane, tw, v);
   if constexpr (NS * R == N) {
     static_for<0, PER>([&](auto pc) {
       constexpr int p = decltype(pc)::value;
-      if ((N / R) % WAVE == 0 || lane + p * WAVE < N / R) {
+      if ((N / R) % L == 0 || lane + p * L < N / R) {
         static_for<0, R>([&](auto rc) {
           constexpr int r = decltype(rc)::value;
-          emit(ic<p * WAVE + r * NS>{}, v[p][r]);
+          emit(ic<p * L + r * NS>{}, v[p][r]);
         });
       }
     });
   } else {
     constexpr int R2 = pick_radix(N / (NS * R));
-    float2 v2[(N / R2 + WAVE - 1) / WAVE][R2];
-    half_write<N, R, NS, 0>(hbuf, lane, v);
+    float2 v2[(N / R2 + L - 1) / L][R2];
+    half_write<N, R, NS, 0, L>(hbuf, lane, v);
     wave_sync();
-    half_read<N, R2, 0>(hbuf, lane, v2);
+    half_read<N, R2, 0, 0, L>(hbuf, lane, v2);
     wave_sync();
-    half_write<N, R, NS, 1>(hbuf, lane, v);
+    half_write<N, R, NS, 1, L>(hbuf, lane, v);
     wave_sync();
-    half_read<N, R2, 1>(hbuf, lane, v2);
+    half_read<N, R2, 1, 0, L>(hbuf, lane, v2);
     wave_sync();
-    half_chain<N, SIGN, NS * R, 0, CL>(hbuf, lane, tw, v2, emit);
+    half_chain<N, SIGN, NS * R, 0, CL, L>(hbuf, lane, tw, v2, emit);
   }
 }
 
-// Registers of the first stage's inputs: v[p][r] = x[lane + 64 p + r N/R0].
-template <int N>
+// Registers of the first stage's inputs: v[p][r] = x[lane + L p + r N/R0].
+template <int N, int L = WAVE>
 struct HalfIn {
   static constexpr int R = pick_radix(N);
-  static constexpr int PER = (N / R + WAVE - 1) / WAVE;
+  static constexpr int PER = (N / R + L - 1) / L;
   float2 v[PER][R];
 };
 
 // ZB: the zero band of the first stage's inputs (see zero_band; the inputs in
 // it need not have been read into `in`), 0 for none.
-template <int N, int SIGN, int ZB = 0, bool CL = false, class Emit>
+template <int N, int SIGN, int ZB = 0, bool CL = false, int L = WAVE, class Emit>
 __device__ __forceinline__ void wave_fft_half_emit(float2* hbuf, int lane, const float2* __restrict__ tw,
-                                                   HalfIn<N>& in, Emit&& emit) {
+                                                   HalfIn<N, L>& in, Emit&& emit) {
   static_assert(plan_even(N), "half-length exchange needs even radices");
-  half_chain<N, SIGN, 1, ZB, CL>(hbuf, lane, tw, in.v, emit);
+  half_chain<N, SIGN, 1, ZB, CL, L>(hbuf, lane, tw, in.v, emit);
 }
 
 template <int N, int SIGN, int NS = 1>

@@ -2557,6 +2557,119 @@ __global__ void __launch_bounds__(Fft2<N>::THREADS) k_fft_cols(float2* data) {
   }
 }
 
+// Power-of-two sizes from 128 to 2048: the same two passes with the exchanges
+// through half-length LDS buffers (see wave_fft_half_emit), so that twice the
+// wavefronts share a CU, and N / 16 lanes per vector (one first-stage butterfly
+// each) instead of 64, several vectors a wavefront where N < 1024. Rows go from
+// memory to the first stage's registers and from the last stage's to memory.
+// Columns are taken CPW at a time, so that a row of the tile is at least one
+// whole 128-byte line (8 columns a workgroup moved half lines); their lower and
+// upper halves pass through the same buffers, on the way in and out.
+// Bound by memory: two passes over 64 images of 1024^2 (2.1 GB) 685 -> 480 us,
+// 4.5 of the 5.1 TB/s that a copy reaches; 256^2 704 -> 400 us and 2048^2 1082 ->
+// 497 us for as many bytes.
+template <int N>
+struct FftHalf {
+  static constexpr int L = N / 16 < WAVE ? N / 16 : WAVE;   // lanes per vector
+  static constexpr int VPV = WAVE / L;                      // vectors per wavefront
+  // columns start on different bank groups (4 mod 32 complex, as the row pass)
+  static constexpr int STRIDE = padded_len(N / 2) + ((4 - padded_len(N / 2) % 32) + 32) % 32;
+  static constexpr int TW = TwLds<N>::ON ? tw_entries(N) : 0;
+  static constexpr int RWAVES = 8, RPW = RWAVES * VPV;      // rows per workgroup
+  static constexpr int CPW = 4 * VPV > 16 ? 4 * VPV : 16;   // columns per workgroup
+  static constexpr int CWAVES = CPW / VPV;
+  static constexpr size_t row_lds() { return (size_t)(RPW * STRIDE + TW) * sizeof(float2); }
+  static constexpr size_t col_lds() { return (size_t)(CPW * STRIDE + TW) * sizeof(float2); }
+};
+template <int N>
+constexpr bool fft_half() { return plan_even(N) && N >= 128 && N <= 2048; }
+
+template <int N, int SIGN>
+__global__ void __launch_bounds__(FftHalf<N>::RWAVES * WAVE) k_fft_rows_half(const float2* in, float2* out, int nrows) {
+  using F_ = FftHalf<N>;
+  constexpr int L = F_::L, R = HalfIn<N, L>::R, PER = HalfIn<N, L>::PER;
+  extern __shared__ float4 lds_raw[];
+  float2* lds = reinterpret_cast<float2*>(lds_raw);
+  const int vec = threadIdx.x / L, lane = threadIdx.x % L;  // vector of the workgroup, lane within it
+  const long row = (long)blockIdx.x * F_::RPW + vec;
+  const float2* s = in + min(row, (long)nrows - 1) * N;     // (spare vectors repeat the last row)
+  HalfIn<N, L> x;
+#pragma unroll
+  for (int p = 0; p < PER; ++p)
+#pragma unroll
+    for (int r = 0; r < R; ++r) x.v[p][r] = s[lane + L * p + r * (N / R)];
+  const float2* tw = stage_twiddles<N>(lds + F_::RPW * F_::STRIDE);
+  if (TwLds<N>::ON) __syncthreads();
+  float2* d = out + row * N;
+  wave_fft_half_emit<N, SIGN, 0, false, L>(lds + vec * F_::STRIDE, lane, tw, x, [&](auto qb, float2 v) {
+    if (row < nrows) d[decltype(qb)::value + lane] = v;
+  });
+}
+
+template <int N, int SIGN>
+__global__ void __launch_bounds__(FftHalf<N>::CWAVES * WAVE) k_fft_cols_half(float2* data) {
+  using F_ = FftHalf<N>;
+  constexpr int L = F_::L, CPW = F_::CPW, ST = F_::STRIDE, H = N / 2, THR = F_::CWAVES * WAVE;
+  constexpr int R = HalfIn<N, L>::R, PER = HalfIn<N, L>::PER;
+  constexpr int Q = CPW / 2, ROWS = THR / Q, EPT = H / ROWS;   // float4 of a tile row; rows at once; per thread and half
+  static_assert(H % ROWS == 0 && N % CPW == 0, "whole tiles");
+  constexpr int RL = pick_radix(N / last_stage_ns(N)), PL = N / RL / L;   // last stage: radix, butterflies per lane
+  extern __shared__ float4 lds_raw[];
+  float2* lds = reinterpret_cast<float2*>(lds_raw);
+  const int vec = threadIdx.x / L, lane = threadIdx.x % L;
+  float4* img = reinterpret_cast<float4*>(data + (size_t)blockIdx.y * N * N + blockIdx.x * CPW);
+  const int q = threadIdx.x % Q, r0 = threadIdx.x / Q;
+  float4 t[EPT];
+  auto load = [&](int half) {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) t[e] = img[(size_t)(half * H + r0 + e * ROWS) * (N / 2) + q];
+  };
+  auto put = [&]() {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      float2* d = lds + 2 * q * ST + pad(r0 + e * ROWS);
+      d[0] = make_float2(t[e].x, t[e].y);
+      d[ST] = make_float2(t[e].z, t[e].w);
+    }
+  };
+  auto store = [&](int half) {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const float2* s = lds + 2 * q * ST + pad(r0 + e * ROWS);
+      const float2 a = s[0], b = s[ST];
+      img[(size_t)(half * H + r0 + e * ROWS) * (N / 2) + q] = make_float4(a.x, a.y, b.x, b.y);
+    }
+  };
+  const float2* tw = stage_twiddles<N>(lds + CPW * ST);
+  float2* buf = lds + vec * ST;                              // this vector's column
+  HalfIn<N, L> x;
+  load(0);
+  put();
+  load(1);
+  __syncthreads();
+  half_read<N, R, 0, 0, L>(buf, lane, x.v);
+  __syncthreads();
+  put();
+  __syncthreads();
+  half_read<N, R, 1, 0, L>(buf, lane, x.v);
+  wave_sync();
+  float2 up[PL][RL / 2];                                     // the outputs from N / 2 on
+  wave_fft_half_emit<N, SIGN, 0, false, L>(buf, lane, tw, x, [&](auto qb, float2 v) {
+    constexpr int QB = decltype(qb)::value, r = QB / (N / RL), p = QB % (N / RL) / L;
+    if constexpr (QB < H) buf[pad(QB + lane)] = v;
+    else up[p][r - RL / 2] = v;
+  });
+  __syncthreads();
+  store(0);
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < PL; ++p)
+#pragma unroll
+    for (int r = 0; r < RL / 2; ++r) buf[pad(p * L + r * (N / RL) + lane)] = up[p][r];
+  __syncthreads();
+  store(1);
+}
+
 // ============================================================== adjoint
 // Weight sums alone (the adjoint needs 1/W before anything else): counts of
 // kept entries (natural) or occupied cells (uniform) per half-spectrum column.
