@@ -771,18 +771,7 @@ void launch_xe_all(const XeArgs& a, hipStream_t st) {
 
 #define BLINK_DISPATCH_N(n, CALL)                                    \
   switch (n) {                                                       \
-    case 8: return CALL(8);                                          \
-    case 12: return CALL(12);                                        \
-    case 16: return CALL(16);                                        \
-    case 32: return CALL(32);                                        \
-    case 64: return CALL(64);                                        \
-    case 128: return CALL(128);                                      \
-    case 180: return CALL(180);                                      \
-    case 256: return CALL(256);                                      \
     case 512: return CALL(512);                                      \
-    case 1024: return CALL(1024);                                    \
-    case 2048: return CALL(2048);                                    \
-    case 4096: return CALL(4096);                                    \
     default: return BLINK_E_UNSUPPORTED;                             \
   }
 

@@ -1045,42 +1045,53 @@ __device__ __forceinline__ void step_gather(const ImgArgs& a, int t, int ch, dou
 // plain read-modify-write. The column being gridded is LDS that only its own
 // wavefront writes, so the adds are done as plain read-modify-writes, and
 // lanes that would touch the same element take turns: each turn, every
-// pending lane posts a tag (turn * 64 + 64 - lane) to claim slot key mod 64
-// with an integer atomic max, and the lane whose tag survives adds its value
-// (and, with counts, 1 to its count). Lanes whose elements coincide share a
+// pending lane posts a tag (turn * 64 + 64 - lane) to its key's claim slot
+// with an integer atomic max, and the lane whose tag survives adds its value. Lanes whose elements coincide share a
 // slot, so no two lanes of one turn touch one element; of the lanes sharing
 // a slot the lowest goes first, so each element receives its adds in lane
 // order, step after step: the order of the sorted list, whatever the
 // grouping into steps. Tags grow with the wavefront's turn counter, so the
 // claim slots never need clearing after their initial zeroing.
-constexpr int CLAIM_SLOTS = 64;
+// Slots: a column buffer of up to 256 rows has one per row, so that only lanes
+// that really meet on a row wait for each other (2.7 instead of 4 turns a step
+// of the all-sky columns); for longer buffers the words would cost a workgroup
+// per CU, and key mod 64 stays.
+constexpr int CLAIM_TAG = 64;    // tags per turn
+__host__ __device__ constexpr int claim_slots(int rows) {
+  int n = 64;
+  while (n < rows) n *= 2;
+  return n <= 256 ? n : 64;
+}
 
+template <int SLOTS>
 struct Claim {
-  unsigned* slot;                // CLAIM_SLOTS words of this wavefront's LDS
+  unsigned* slot;                // SLOTS words of this wavefront's LDS
   unsigned turn;                 // wave-uniform
 };
 
 // Zeroes this wavefront's claim slots (the caller's next wave_sync publishes them).
-__device__ __forceinline__ Claim claim_init(unsigned* slots, int lane) {
-  if (lane < CLAIM_SLOTS) slots[lane] = 0u;
-  return Claim{slots, 0u};
+template <int SLOTS>
+__device__ __forceinline__ Claim<SLOTS> claim_init(unsigned* slots, int lane) {
+  for (int i = lane; i < SLOTS; i += WAVE) slots[i] = 0u;
+  return Claim<SLOTS>{slots, 0u};
 }
 
 // dst[idx] += v (and cnt[cidx] += 1 with COUNT) for every active lane; lanes
-// with equal idx must pass equal key.
-template <bool COUNT>
+// with equal idx must pass equal key. Counts are integers, so they take one
+// atomic a step outside the turns.
+template <bool COUNT, int SLOTS>
 __device__ __forceinline__ void wave_add(float2* dst, int idx, int* cnt, int cidx, int key, float2 v, bool active,
-                                         Claim& cl, int lane) {
+                                         Claim<SLOTS>& cl, int lane) {
+  if (COUNT && active) __hip_atomic_fetch_add(cnt + cidx, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
   bool pending = active;
   while (__ballot(pending) != 0) {
-    const unsigned tag = cl.turn * CLAIM_SLOTS + (unsigned)(CLAIM_SLOTS - lane);
-    unsigned* slot = cl.slot + (key & (CLAIM_SLOTS - 1));
+    const unsigned tag = cl.turn * CLAIM_TAG + (unsigned)(CLAIM_TAG - lane);
+    unsigned* slot = cl.slot + (key & (SLOTS - 1));
     if (pending) __hip_atomic_fetch_max(slot, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     wave_sync();
     if (pending && *slot == tag) {
       const float2 d = dst[idx];
       dst[idx] = make_float2(d.x + v.x, d.y + v.y);
-      if (COUNT) cnt[cidx] += 1;
       pending = false;
     }
     wave_sync();
@@ -1089,8 +1100,8 @@ __device__ __forceinline__ void wave_add(float2* dst, int idx, int* cnt, int cid
 }
 
 // phase 3: the LDS adds; kd / kc count the kept direct / conjugate entries
-template <bool COUNT>
-__device__ __forceinline__ void step_add(const EntryStep& e, float2* buf, int* cnt, int& kd, int& kc, Claim& cl,
+template <bool COUNT, int SLOTS>
+__device__ __forceinline__ void step_add(const EntryStep& e, float2* buf, int* cnt, int& kd, int& kc, Claim<SLOTS>& cl,
                                          int lane) {
 #pragma unroll
   for (int u = 0; u < GU; ++u) {
@@ -1105,20 +1116,24 @@ __device__ __forceinline__ void step_add(const EntryStep& e, float2* buf, int* c
 // All steps of a column from step i0 on; returns the kept direct and
 // conjugate entries (added to kd / kc). The phase-rotated form is a separate
 // copy of the loop, so the plain one carries none of its work.
-template <int N, bool COUNT, bool ROT>
+template <int N, bool COUNT, bool ROT, int SLOTS>
 __device__ __forceinline__ void grid_steps_t(const ImgArgs& a, const ColSpan& c, int i0, float2* buf, int* cnt,
-                                             int t, int ch, double s, int lane, int& kd, int& kc, Claim& cl) {
+                                             int t, int ch, double s, int lane, int& kd, int& kc, Claim<SLOTS>& cl) {
   const int total = c.total();
+  EntryStep e;
+  if (i0 < total) step_keys<ROT>(a, c, i0, t, lane, e);
   for (; i0 < total; i0 += GU * WAVE) {
-    EntryStep e;
-    step_keys<ROT>(a, c, i0, t, lane, e);
     step_gather<N, ROT>(a, t, ch, s, e);
+    // the next step's lists are in flight during this one's gathers and adds
+    EntryStep nx;
+    if (i0 + GU * WAVE < total) step_keys<ROT>(a, c, i0 + GU * WAVE, t, lane, nx);
     step_add<COUNT>(e, buf, cnt, kd, kc, cl, lane);
+    e = nx;
   }
 }
-template <int N, bool COUNT>
+template <int N, bool COUNT, int SLOTS>
 __device__ __forceinline__ void grid_steps(const ImgArgs& a, const ColSpan& c, int i0, float2* buf, int* cnt,
-                                           int t, int ch, double s, int lane, int& kd, int& kc, Claim& cl) {
+                                           int t, int ch, double s, int lane, int& kd, int& kc, Claim<SLOTS>& cl) {
   if (a.sd != nullptr) grid_steps_t<N, COUNT, true>(a, c, i0, buf, cnt, t, ch, s, lane, kd, kc, cl);
   else grid_steps_t<N, COUNT, false>(a, c, i0, buf, cnt, t, ch, s, lane, kd, kc, cl);
 }
@@ -1176,13 +1191,13 @@ __device__ __forceinline__ float kb_inv_taper(double xi, const ImgArgs& a) {
 // wave_add, keyed on j0), and lanes with different j0 never reach the same
 // row at the same k, so a turn adds all of its lanes' rows in sequence over
 // k. Each element receives its adds in a fixed order: step, turn, k.
-template <int N, bool COUNT, int KMAX>
+template <int N, bool COUNT, int KMAX, int SLOTS>
 __device__ __forceinline__ void kb_add_rows(float2* buf, int* cnt, int j0, int nrow, const float (&w)[KMAX + 1],
-                                            float2 v, bool active, int kw, Claim& cl, int lane) {
+                                            float2 v, bool active, int kw, Claim<SLOTS>& cl, int lane) {
   bool pending = active;
   while (__ballot(pending) != 0) {
-    const unsigned tag = cl.turn * CLAIM_SLOTS + (unsigned)(CLAIM_SLOTS - lane);
-    unsigned* slot = cl.slot + (j0 & (CLAIM_SLOTS - 1));
+    const unsigned tag = cl.turn * CLAIM_TAG + (unsigned)(CLAIM_TAG - lane);
+    unsigned* slot = cl.slot + (j0 & (SLOTS - 1));
     if (pending) __hip_atomic_fetch_max(slot, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     wave_sync();
     const bool go = pending && *slot == tag;
@@ -1211,10 +1226,10 @@ __device__ __forceinline__ void kb_add_rows(float2* buf, int* cnt, int j0, int n
 // row weights are formed first (KMAX >= W bounds them at compile time), then
 // kb_add_rows adds them. kd / kc count kept entries whose nearest column is
 // c (each baseline once); wsum collects this lane's weights.
-template <int N, bool COUNT, int KMAX>
+template <int N, bool COUNT, int KMAX, int SLOTS>
 __device__ __forceinline__ void grid_steps_kb(const ImgArgs& a, const ColSpan& sp, int c, float2* buf,
                                               int* cnt, int t, int ch, double s, int lane, int& kd,
-                                              int& kc, float& wsum, Claim& cl, const int* dens) {
+                                              int& kc, float& wsum, Claim<SLOTS>& cl, const int* dens) {
   constexpr int H = N / 2;
   const size_t tb = (size_t)t * a.B;
   const size_t vb = ((size_t)t * a.C + ch) * a.B;
@@ -1375,7 +1390,8 @@ struct Cols {
     return (size_t)(CPW * STRIDE + TW) * sizeof(float2) + (counts ? (size_t)CPW * N * sizeof(int) : 0);
   }
   // the gridding kernel adds every wavefront's claim slots after that
-  static size_t grid_lds_bytes(bool counts) { return lds_bytes(counts) + (size_t)CPW * CLAIM_SLOTS * sizeof(unsigned); }
+  static constexpr int SLOTS = claim_slots(N);
+  static size_t grid_lds_bytes(bool counts) { return lds_bytes(counts) + (size_t)CPW * SLOTS * sizeof(unsigned); }
 };
 
 // One workgroup = CPW consecutive u-cell columns of one image; one wavefront
@@ -1429,7 +1445,7 @@ __global__ void __launch_bounds__((Cols<N, CPW>::THREADS)) k_grid_cols(ImgArgs a
   if (CNT)
     for (int r = lane; r < N; r += WAVE) cnt[r] = 0;
   unsigned* lclaim = reinterpret_cast<unsigned*>(lcnt + (CNT ? CPW * N : 0));
-  Claim cl = claim_init(lclaim + wave * CLAIM_SLOTS, lane);
+  Claim<C_::SLOTS> cl = claim_init<C_::SLOTS>(lclaim + wave * C_::SLOTS, lane);
   wave_sync();
 
   int kept_b = 0, wcontrib = 0;
@@ -1528,14 +1544,15 @@ struct ColsHalf {
   // 22.5 KB instead of 26.6 KB, so seven workgroups share a CU instead of six
   static constexpr bool CL = TwLds<N>::ON && compact_last(N);
   static constexpr int TW = TwLds<N>::ON ? tw_entries_compact(N) : 0;
+  static constexpr int SLOTS = claim_slots(N / 2);
   static constexpr size_t LDS = (size_t)(CPW * STRIDE + TW) * sizeof(float2) +
                                 (UNI ? (size_t)CPW * (N / 2) * sizeof(int) : 0) +
-                                (size_t)CPW * CLAIM_SLOTS * sizeof(unsigned);
+                                (size_t)CPW * SLOTS * sizeof(unsigned);
 };
 
 // LDS adds (and counts) of the kept entries of a step whose row lies in half HF
-template <int N, int HF, bool COUNT>
-__device__ __forceinline__ void step_add_half(const EntryStep& e, float2* hbuf, int* hcnt, Claim& cl, int lane) {
+template <int N, int HF, bool COUNT, int SLOTS>
+__device__ __forceinline__ void step_add_half(const EntryStep& e, float2* hbuf, int* hcnt, Claim<SLOTS>& cl, int lane) {
 #pragma unroll
   for (int u = 0; u < GU; ++u) {
     const bool act = e.ok[u] && (e.row[u] >= N / 2) == (HF == 1);
@@ -1583,10 +1600,10 @@ __device__ __forceinline__ int uniform_half(float2* hbuf, const int* hcnt, int l
 // column of at most GU x 64 entries (the usual case) keeps its one step of
 // entries in registers for both halves; longer columns load them again.
 // occ: this lane's occupied cells (uniform weighting).
-template <int N, bool ROT, bool UNI, int ZB>
+template <int N, bool ROT, bool UNI, int ZB, int SLOTS>
 __device__ __forceinline__ void grid_col_half(const ImgArgs& a, const ColSpan& c, float2* hbuf, int* hcnt,
                                               HalfIn<N>& in, int t, int ch, double s, int lane, int& kd,
-                                              int& kc, int& occ, Claim& cl) {
+                                              int& kc, int& occ, Claim<SLOTS>& cl) {
   constexpr int R0 = HalfIn<N>::R;
   const int total = c.total();
   const bool one = total <= GU * WAVE;
@@ -1688,7 +1705,7 @@ __global__ void __launch_bounds__((ColsHalf<N, CPW, UNI>::THREADS)) k_grid_cols_
     constexpr int ZB = decltype(zbc)::value;
     HalfIn<N> in;
     int kd = 0, kc = 0, occ = 0;
-    Claim cl = claim_init(lclaim + wave * CLAIM_SLOTS, lane);
+    Claim<C_::SLOTS> cl = claim_init<C_::SLOTS>(lclaim + wave * C_::SLOTS, lane);
     if (a.sd != nullptr) grid_col_half<N, true, UNI, ZB>(a, span, hbuf, hcnt, in, t, ch, s, lane, kd, kc, occ, cl);
     else grid_col_half<N, false, UNI, ZB>(a, span, hbuf, hcnt, in, t, ch, s, lane, kd, kc, occ, cl);
     // baselines counted once: the direct entry of every cell column, plus the
