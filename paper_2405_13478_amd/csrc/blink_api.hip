@@ -636,6 +636,15 @@ blink_status grid_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t st
   return launched();
 }
 
+template <int N, bool UNI>
+void launch_cols_adj_half(ImgArgs& a, int n, hipStream_t st) {
+  constexpr int CPW = N <= 1024 ? 8 : 4;
+  using C_ = ColsHalf<N, CPW, UNI>;
+  a.ntiles = (int)cdiv(N / 2, CPW);
+  hipLaunchKernelGGL((k_cols_adj_half<N, CPW, UNI>), dim3((unsigned)(cdiv(n, 8) * 8LL * a.ntiles)), dim3(C_::THREADS),
+                     C_::LDS, st, a);
+}
+
 template <int N>
 blink_status adjoint_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t st, int sorted) {
   const long long n_img = (long long)p->n_time * p->n_chan;
@@ -673,7 +682,10 @@ blink_status adjoint_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t
         hipLaunchKernelGGL((k_weights<N, false>), gw, dim3(Cols<N>::THREADS), ldsw, st, a);
     }
     const dim3 g2(cdiv(p->out_n / 2, Rows<N>::PPW), n);
-    hipLaunchKernelGGL((k_rows_adj<N>), g2, dim3(Rows<N>::THREADS), Rows<N>::LDS, st, a);
+    if constexpr (rows_half<N>())
+      hipLaunchKernelGGL((k_rows_adj_half<N>), g2, dim3(RowsHalf<N>::THREADS), RowsHalf<N>::LDS, st, a);
+    else
+      hipLaunchKernelGGL((k_rows_adj<N>), g2, dim3(Rows<N>::THREADS), Rows<N>::LDS, st, a);
     // flagged and dropped baselines are never visited: their gradients are zero
     const size_t ng = (size_t)n * a.B;
     hipLaunchKernelGGL(k_fill2, dim3(cdiv((long long)ng, 256)), dim3(256), 0, st,
@@ -690,13 +702,16 @@ blink_status adjoint_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t
         hipLaunchKernelGGL((k_degrid_kb<N, KB_SMALL_SUPPORT>), gd, dim3(256), 0, st, a);
       else
         hipLaunchKernelGGL((k_degrid_kb<N, KB_MAX_SUPPORT>), gd, dim3(256), 0, st, a);
+    } else if constexpr (cols_half<N>()) {
+      if (uni) launch_cols_adj_half<N, true>(a, n, st);
+      else launch_cols_adj_half<N, false>(a, n, st);
     } else if (uni) {
       hipLaunchKernelGGL((k_cols_adj<N, true>), g1, dim3(Cols<N>::THREADS), lds1, st, a);
     } else {
       hipLaunchKernelGGL((k_cols_adj<N, false>), g1, dim3(Cols<N>::THREADS), lds1, st, a);
     }
     if (a.gains)
-      hipLaunchKernelGGL(k_gq_reduce, dim3(cdiv(a.B, 64)), dim3(256), 0, st, a);
+      hipLaunchKernelGGL(k_gq_reduce, dim3(cdiv(a.B, 64)), dim3(64 * GQ_SLICES), 0, st, a);
   }
   if (a.gains && a.gain_grad)
     hipLaunchKernelGGL(k_gain_grad, dim3(p->n_ant), dim3(256), 0, st, a);
@@ -771,7 +786,18 @@ void launch_xe_all(const XeArgs& a, hipStream_t st) {
 
 #define BLINK_DISPATCH_N(n, CALL)                                    \
   switch (n) {                                                       \
+    case 8: return CALL(8);                                          \
+    case 12: return CALL(12);                                        \
+    case 16: return CALL(16);                                        \
+    case 32: return CALL(32);                                        \
+    case 64: return CALL(64);                                        \
+    case 128: return CALL(128);                                      \
+    case 180: return CALL(180);                                      \
+    case 256: return CALL(256);                                      \
     case 512: return CALL(512);                                      \
+    case 1024: return CALL(1024);                                    \
+    case 2048: return CALL(2048);                                    \
+    case 4096: return CALL(4096);                                    \
     default: return BLINK_E_UNSUPPORTED;                             \
   }
 

@@ -2924,6 +2924,291 @@ __global__ void __launch_bounds__(Cols<N>::THREADS) k_cols_adj(ImgArgs a) {
   }
 }
 
+// The gradient of one gridded baseline from the column gradient g at its cell:
+// the conjugate of the rotation / cable factor, then vis_grad = conj(g1 conj g2)
+// gamma' and, with gains, gq = gamma' conj(V).
+__device__ __forceinline__ void put_vis_grad(const ImgArgs& a, int li, int img, int ch, size_t tb, int j, float2 g) {
+  const size_t vb = (size_t)img * a.B;
+  const int b = a.perm[tb + j];
+  if (a.sd != nullptr) g = rotate_phase(g, -a.sd[tb + j], a.freq[ch]);
+  if (a.gains) {
+    a.vis_grad[vb + b] = cmul(cconj(baseline_gain(a, b)), g);
+    const float2 v = load_vis_raw(a, vb + b, ch);
+    a.gamma[(size_t)li * a.B + b] = cmul(g, cconj(v));
+  } else {
+    a.vis_grad[vb + b] = g;
+  }
+}
+
+// First-stage inputs of the adjoint's forward transforms straight from memory:
+// x[q] = value(q') for the M cutout positions (q' = q + M/2 mod N < M), zero
+// elsewhere. ZB: the zero band of a cutout of at most N - ZB N/16 points, whose
+// inputs are not formed.
+template <int N, int ZB, class Value>
+__device__ __forceinline__ void cutout_inputs(HalfIn<N>& in, int lane, int M, Value&& value) {
+  constexpr int R = HalfIn<N>::R, PER = HalfIn<N>::PER;
+  constexpr int zlo = R / 2 - ZB / 2, zhi = R / 2 + ZB / 2;
+#pragma unroll
+  for (int p = 0; p < PER; ++p)
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (r < zlo || r >= zhi) {
+        const int q = lane + p * WAVE + r * (N / R);
+        const int m = r < R / 2 ? q + M / 2 : q + M / 2 - N;        // position in the cutout
+        const bool in_cut = (N / R % WAVE == 0 || lane + p * WAVE < N / R) && m >= 0 && m < M;
+        in.v[p][r] = in_cut ? value(m) : make_float2(0.f, 0.f);
+      }
+}
+// Cutouts of up to half of the grid leave the middle half of every
+// transform's inputs zero.
+template <int N>
+constexpr bool adj_band() { return HalfIn<N>::R == 16; }
+
+// k_rows_adj for power-of-two sizes up to 2048: the rows go from memory to the
+// first stage's registers (the empty middle half of a cutout M <= N/2 is neither
+// read nor added), the exchanges pass through half-length buffers, and the
+// Hermitian split reads Z[k] from the lower half of the outputs and Z[N - k] from
+// the upper one through the same buffers.
+template <int N>
+__global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_adj_half(ImgArgs a) {
+  using R_ = RowsHalf<N>;
+  constexpr int H = N / 2, PPW = R_::PPW, ST = R_::STRIDE, THR = R_::THREADS;
+  constexpr int EPT = (H * PPW + THR - 1) / THR;
+  constexpr int RL = pick_radix(N / last_stage_ns(N)), PL = (N / RL + WAVE - 1) / WAVE;
+  extern __shared__ float4 lds_raw[];
+  float2* lds = reinterpret_cast<float2*>(lds_raw);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = threadIdx.x % WAVE;
+  const int li = blockIdx.y;
+  const int img = a.img0 + li;
+  const int M = a.M;
+  const int npair = M / 2;
+  const int p0 = blockIdx.x * PPW;
+  const int nz = min(H, a.ncz[img]);
+  const float W = a.wsum_in ? a.wsum_in[img]
+                  : a.kw > 0 ? sum_partials_f(a.wpart, img, a.wstride, a.wtiles, lane)
+                             : (float)sum_partials(a.wpart, img, a.wstride, a.wtiles, lane);
+  const float scale = a.norm ? (W > 0 ? 1.0f / W : 0.0f) : 1.0f;
+  const float2* tw = stage_twiddles<N>(lds + PPW * ST);
+  const int pair = min(p0 + wave, npair - 1);                  // (spare wavefronts repeat the last pair)
+  const float* g0 = a.image_grad + ((size_t)img * M + 2 * pair) * M;
+  const float* g1 = g0 + M;
+  // with a gridding kernel the forward pass divided pixel (m, l) by
+  // c(q_m / N) c(q_l / N); that diagonal scaling is its own adjoint
+  float s0 = scale, s1 = scale;
+  if (a.kw > 0) {
+    s0 *= kb_inv_taper((double)(2 * pair - M / 2) / N, a);
+    s1 *= kb_inv_taper((double)(2 * pair + 1 - M / 2) / N, a);
+  }
+  if (TwLds<N>::ON) __syncthreads();                           // the twiddles
+  float2* z = lds + wave * ST;
+  float2 up[PL][RL / 2];                                       // the outputs from N / 2 on
+  auto body = [&](auto zbc) {
+    constexpr int ZB = decltype(zbc)::value;
+    HalfIn<N> in;
+    cutout_inputs<N, ZB>(in, lane, M, [&](int l) {
+      const float cl = a.kw > 0 ? kb_inv_taper((double)(l - M / 2) / N, a) : 1.0f;
+      return make_float2(g0[l] * s0 * cl, g1[l] * s1 * cl);
+    });
+    wave_fft_half_emit<N, -1, ZB>(z, lane, tw, in, [&](auto qb, float2 v) {
+      constexpr int QB = decltype(qb)::value, r = QB / (N / RL), p = QB % (N / RL) / WAVE;
+      if constexpr (QB < H) z[pad(QB + lane)] = v;
+      else up[p][r - RL / 2] = v;
+    });
+  };
+  if (adj_band<N>() && 2 * M <= N) body(ic<adj_band<N>() ? 8 : 0>{});
+  else body(ic<0>{});
+  __syncthreads();
+  // thread t takes pair slot t % PPW and columns t / PPW + i (THR / PPW)
+  const int kt = threadIdx.x / PPW, pt = threadIdx.x % PPW;
+  const float2* zs = lds + pt * ST;
+  float2 zk[EPT];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int k = kt + i * (THR / PPW);
+    zk[i] = k < nz ? zs[pad(k)] : make_float2(0.f, 0.f);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < PL; ++p)
+    if ((N / RL) % WAVE == 0 || lane + p * WAVE < N / RL)
+#pragma unroll
+      for (int r = 0; r < RL / 2; ++r) z[pad(p * WAVE + r * (N / RL) + lane)] = up[p][r];
+  __syncthreads();
+  float4* dst = reinterpret_cast<float4*>(a.half + (size_t)li * H * M);
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int k = kt + i * (THR / PPW);
+    if (k < nz && p0 + pt < npair) {
+      float4 o;
+      if (k == 0) {
+        o = make_float4(zk[i].x, 0.f, zk[i].y, 0.f);
+      } else {  // 2 A[k] = Z[k] + conj Z[N-k]; 2 B[k] = -i (Z[k] - conj Z[N-k])
+        const float2 zm = zs[pad(H - k)];
+        o = make_float4(zk[i].x + zm.x, zk[i].y - zm.y, zk[i].y + zm.y, -(zk[i].x - zm.x));
+      }
+      dst[(size_t)k * (M / 2) + p0 + pt] = o;
+    }
+  }
+}
+
+// k_cols_adj for power-of-two sizes up to 2048 (nearest cell): the column goes
+// from memory to the first stage's registers, the exchanges pass through a
+// half-length buffer, and the entries are gathered from the lower half of the
+// transformed column, then from the upper one. Columns of at most GADJ x 64
+// entries (the usual case) keep their rows in registers for both. The u = 0
+// column adds each entry's two rows, which lie in different halves: its lower
+// half waits in registers (`low`, one value per kept entry) or, for longer
+// columns, in the entry's vis_grad slot.
+constexpr int GADJ = 4;
+
+template <int N, int CPW, bool UNI>
+__global__ void __launch_bounds__((ColsHalf<N, CPW, UNI>::THREADS)) k_cols_adj_half(ImgArgs a) {
+  using C_ = ColsHalf<N, CPW, UNI>;
+  constexpr int H = N / 2;
+  constexpr int RL = pick_radix(N / last_stage_ns(N)), PL = (N / RL + WAVE - 1) / WAVE;
+  extern __shared__ float4 lds_raw[];
+  const int L = blockIdx.x;
+  const int r8 = L >> 3;
+  const int li = (r8 / a.ntiles) * 8 + (L & 7);
+  const int tile = r8 % a.ntiles;
+  if (li >= a.nimg) return;
+  const int img = a.img0 + li;
+  const int nz = min(H, a.ncz[img]);
+  const int c0 = tile * CPW;
+  if (c0 >= nz) return;                               // no baseline lives in this tile
+  float2* lds = reinterpret_cast<float2*>(lds_raw);
+  float2* ltw = lds + CPW * C_::STRIDE;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = threadIdx.x % WAVE;
+  const int t = img / a.C, ch = img - t * a.C;
+  const int cs = c0 + wave;
+  float2* buf = lds + wave * C_::STRIDE;
+  int* cnt = UNI ? reinterpret_cast<int*>(ltw + C_::TW) + wave * H : nullptr;
+  const double s = cells_per_metre(a.freq[ch], a.ndx);
+  const int M = a.M;
+  const float2* tw = stage_twiddles<N, C_::CL>(ltw);
+  if (TwLds<N>::ON) __syncthreads();
+  if (cs >= nz) return;
+  const float2* srcc = a.half + ((size_t)li * H + cs) * M;
+  float2 up[PL][RL / 2];                              // the outputs from N / 2 on
+  auto body = [&](auto zbc) {
+    constexpr int ZB = decltype(zbc)::value;
+    HalfIn<N> in;
+    cutout_inputs<N, ZB>(in, lane, M, [&](int m) { return srcc[m]; });
+    wave_fft_half_emit<N, -1, ZB, C_::CL>(buf, lane, tw, in, [&](auto qb, float2 v) {
+      constexpr int QB = decltype(qb)::value, r = QB / (N / RL), p = QB % (N / RL) / WAVE;
+      if constexpr (QB < H) buf[pad(QB + lane)] = v;
+      else up[p][r - RL / 2] = v;
+    });
+  };
+  if (adj_band<N>() && 2 * M <= N) body(ic<adj_band<N>() ? 8 : 0>{});
+  else body(ic<0>{});
+  const int* bnd = a.bnd + (size_t)img * (N + 2);
+  const ColSpan c{bnd[cs + H], bnd[cs + 1 + H], bnd[-cs + H], bnd[-cs + 1 + H]};
+  const size_t tb = (size_t)t * a.B;
+  const int nd = c.nd(), total = cs == 0 ? nd : c.total();   // u = 0: its mirror column is itself
+  // entry i of the column: its sorted position and its row (N when not kept);
+  // mirrored entries take their own row's mirror
+  auto entry = [&](int i, int& j, int& row) {
+    const bool cj = i >= nd;
+    j = cj ? c.clo + (i - nd) : c.dlo + i;
+    row = N;
+    if (i < total) {
+      const double iv = rint(a.sv[tb + j] * s);
+      if (fabs(iv) < (double)H) {
+        int r = (int)iv;
+        if (cj) r = -r;
+        row = r < 0 ? r + N : r;
+      }
+    }
+  };
+  int rows[GADJ], js[GADJ];
+#pragma unroll
+  for (int u = 0; u < GADJ; ++u) entry(u * WAVE + lane, js[u], rows[u]);
+  float2 low[GADJ];
+#pragma unroll
+  for (int u = 0; u < GADJ; ++u) low[u] = make_float2(0.f, 0.f);
+  auto half = [&](auto hfc) {
+    constexpr int HF = decltype(hfc)::value;
+    if (UNI) {                                        // cell counts of this half
+      for (int r = lane; r < H; r += WAVE) cnt[r] = 0;
+      wave_sync();
+      for (int i0 = 0; i0 < c.total(); i0 += WAVE) {
+        const int i = i0 + lane;
+        const bool cj = i >= nd;
+        const int j = cj ? c.clo + (i - nd) : c.dlo + i;
+        if (i < c.total()) {
+          const double iv = rint(a.sv[tb + j] * s);
+          if (fabs(iv) < (double)H) {
+            int r = (int)iv;
+            if (cj) r = -r;
+            r = r < 0 ? r + N : r;
+            if ((r >= H) == (HF == 1)) atomicAdd(&cnt[r - HF * H], 1);
+          }
+        }
+      }
+    }
+    wave_sync();
+    auto at = [&](int row) {                          // the column gradient at a row of this half
+      float2 v = buf[pad(row - HF * H)];
+      if (UNI) v = cscale(v, 1.0f / (float)cnt[row - HF * H]);
+      return v;
+    };
+    // what this half adds to an entry: direct G[row] if the row lies here,
+    // conjugated for mirrored entries; at u = 0 also conj G[mirror row]
+    auto part = [&](int i, int row, float2& g) -> bool {
+      bool any = false;
+      if (row != N && (row >= H) == (HF == 1)) {
+        const float2 v = at(row);
+        g = cadd(g, i >= nd ? cconj(v) : v);
+        any = true;
+      }
+      if (cs == 0 && row != N) {
+        const int rm = row == 0 ? 0 : N - row;
+        if ((rm >= H) == (HF == 1)) {
+          g = cadd(g, cconj(at(rm)));
+          any = true;
+        }
+      }
+      return any;
+    };
+#pragma unroll
+    for (int u = 0; u < GADJ; ++u) {
+      const int i = u * WAVE + lane;
+      if (cs == 0) {                                  // both halves contribute: written after the second
+        part(i, rows[u], low[u]);
+        if (HF == 1 && rows[u] != N) put_vis_grad(a, li, img, ch, tb, js[u], low[u]);
+      } else {
+        float2 g = make_float2(0.f, 0.f);
+        if (part(i, rows[u], g)) put_vis_grad(a, li, img, ch, tb, js[u], g);
+      }
+    }
+    for (int i0 = GADJ * WAVE; i0 < total; i0 += WAVE) {
+      int j, row;
+      entry(i0 + lane, j, row);
+      if (row == N) continue;
+      float2 g = make_float2(0.f, 0.f);
+      if (cs == 0) {
+        float2* keep = a.vis_grad + (size_t)img * a.B + a.perm[tb + j];
+        if (HF == 1) g = *keep;
+        part(i0 + lane, row, g);
+        if (HF == 0) *keep = g;
+        else put_vis_grad(a, li, img, ch, tb, j, g);
+      } else if (part(i0 + lane, row, g)) {
+        put_vis_grad(a, li, img, ch, tb, j, g);
+      }
+    }
+  };
+  half(ic<0>{});
+  wave_sync();
+#pragma unroll
+  for (int p = 0; p < PL; ++p)
+    if ((N / RL) % WAVE == 0 || lane + p * WAVE < N / RL)
+#pragma unroll
+      for (int r = 0; r < RL / 2; ++r) buf[pad(p * WAVE + r * (N / RL) + lane)] = up[p][r];
+  wave_sync();
+  half(ic<1>{});
+}
+
 // Adjoint of kernel gridding: gamma'_b = sum over b's footprint cells (j, i)
 // of C(i - x_u) C(j - x_v) G2[j][i], G2 = 2 Gh over the whole plane, taken
 // from the transformed half-spectrum columns B in a.gfull: G2[j][i] = B[j][i]
@@ -2999,18 +3284,25 @@ __global__ void k_fill2(float2* p, size_t n) {
 }
 
 // pacc[b] += sum over this chunk's images of gq[li][b]: 64 baselines per
-// workgroup, 4 image slices per baseline, slices combined in a fixed order.
-__global__ void __launch_bounds__(256) k_gq_reduce(ImgArgs a) {
-  __shared__ float2 part[4][64];
+// workgroup, GQ_SLICES image slices per baseline (a wavefront each), slices
+// combined in a fixed order. The slices hide the latency of the loads: of 320
+// images 4 slices read 80 in sequence (26 us), 16 slices 20.
+constexpr int GQ_SLICES = 16;
+__global__ void __launch_bounds__(64 * GQ_SLICES) k_gq_reduce(ImgArgs a) {
+  __shared__ float2 part[GQ_SLICES][64];
   const int bl = threadIdx.x & 63, sl = threadIdx.x >> 6;
   const int b = blockIdx.x * 64 + bl;
   float2 acc = make_float2(0.f, 0.f);
   if (b < a.B)
-    for (int li = sl; li < a.nimg; li += 4) acc = cadd(acc, a.gamma[(size_t)li * a.B + b]);
+#pragma unroll 4
+    for (int li = sl; li < a.nimg; li += GQ_SLICES) acc = cadd(acc, a.gamma[(size_t)li * a.B + b]);
   part[sl][bl] = acc;
   __syncthreads();
-  if (sl == 0 && b < a.B)
-    a.pacc[b] = cadd(a.pacc[b], cadd(cadd(part[0][bl], part[1][bl]), cadd(part[2][bl], part[3][bl])));
+  if (sl == 0 && b < a.B) {
+    float2 sum = a.pacc[b];
+    for (int i = 0; i < GQ_SLICES; ++i) sum = cadd(sum, part[i][bl]);
+    a.pacc[b] = sum;
+  }
 }
 
 // gain_grad[a] = sum_{b: a1 = a} g2 p_b + sum_{b: a2 = a} g1 conj(p_b)
@@ -3018,11 +3310,23 @@ __global__ void __launch_bounds__(256) k_gain_grad(ImgArgs a) {
   __shared__ float2 part[256];
   const int ant = blockIdx.x;
   float2 acc = make_float2(0.f, 0.f);
-  for (int b = threadIdx.x; b < a.B; b += blockDim.x) {
-    const int a1 = a.ant1[b], a2 = a.ant2[b];
-    const float2 p = a.pacc[b];
-    if (a1 == ant) acc = cadd(acc, cmul(antenna_gain(a.gains, a2, a.n_ant), p));
-    if (a2 == ant) acc = cadd(acc, cmul(antenna_gain(a.gains, a1, a.n_ant), cconj(p)));
+  constexpr int U = 4;                                 // baselines in flight per thread
+  for (int b0 = threadIdx.x; b0 < a.B; b0 += U * 256) {
+    int a1[U], a2[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int b = b0 + u * 256;
+      a1[u] = b < a.B ? a.ant1[b] : -1;
+      a2[u] = b < a.B ? a.ant2[b] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int b = b0 + u * 256;
+      if (b >= a.B || (a1[u] != ant && a2[u] != ant)) continue;
+      const float2 p = a.pacc[b];
+      if (a1[u] == ant) acc = cadd(acc, cmul(antenna_gain(a.gains, a2[u], a.n_ant), p));
+      if (a2[u] == ant) acc = cadd(acc, cmul(antenna_gain(a.gains, a1[u], a.n_ant), cconj(p)));
+    }
   }
   part[threadIdx.x] = acc;
   __syncthreads();
