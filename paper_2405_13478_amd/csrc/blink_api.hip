@@ -612,12 +612,13 @@ blink_status grid_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t st
   const long long n_img = (long long)p->n_time * p->n_chan;
   const bool uni = p->weighting == BLINK_UNIFORM;
   const size_t lds1 = Cols<N>::grid_lds_bytes(true);
-  a.wtiles = (int)cdiv(N, Cols<N>::CPW);
+  const int cpw = p->kernel_support > 0 ? Cols<N>::CPW : GridWr<N>::CPW;
+  a.wtiles = (int)cdiv(N, cpw);
   if (!(sorted & SORTED_BOUNDS)) run_bounds(a, n_img, st);
   for (long long i0 = 0; i0 < n_img; i0 += chunk) {
     const int n = (int)std::min<long long>(chunk, n_img - i0);
     a.img0 = (int)i0; a.nimg = n;
-    a.ntiles = (int)cdiv(N, Cols<N>::CPW);
+    a.ntiles = a.wtiles;
     const dim3 g1((unsigned)(cdiv(n, 8) * 8LL * a.ntiles));
     if (a.kdens != nullptr) launch_kb_density<N>(a, n, st);
     if (p->kernel_support > KB_SMALL_SUPPORT)
@@ -627,12 +628,12 @@ blink_status grid_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t st
       hipLaunchKernelGGL((k_grid_cols<N, MODE_GRID, false, Cols<N>::CPW, true, KB_SMALL_SUPPORT>), g1,
                          dim3(Cols<N>::THREADS), lds1, st, a);
     else if (uni)
-      hipLaunchKernelGGL((k_grid_cols<N, MODE_GRID, true>), g1, dim3(Cols<N>::THREADS), lds1, st, a);
+      hipLaunchKernelGGL((k_grid_write<N, true>), g1, dim3(GridWr<N>::THREADS), GridWr<N>::LDS, st, a);
     else
-      hipLaunchKernelGGL((k_grid_cols<N, MODE_GRID, false>), g1, dim3(Cols<N>::THREADS), lds1, st, a);
+      hipLaunchKernelGGL((k_grid_write<N, false>), g1, dim3(GridWr<N>::THREADS), GridWr<N>::LDS, st, a);
   }
   if (a.weight_sum || a.n_dropped)
-    hipLaunchKernelGGL(k_grid_finish, dim3(cdiv(n_img, 256)), dim3(256), 0, st, a, (int)n_img);
+    hipLaunchKernelGGL(k_grid_finish, dim3(cdiv(n_img, 256 / WAVE)), dim3(256), 0, st, a, (int)n_img);
   return launched();
 }
 
