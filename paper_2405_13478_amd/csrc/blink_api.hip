@@ -478,12 +478,16 @@ void launch_cols_half(ImgArgs& a, int n, hipStream_t st) {
   hipLaunchKernelGGL((k_grid_cols_half<N, CPW, UNI>), g1, dim3(C_::THREADS), C_::LDS, st, a);
 }
 
-// Power-of-two sizes up to 2048 take the column kernel whose exchanges go
-// through half-length LDS buffers (measured at N = 1024, natural weighting:
-// 4.52 ms per 7,680 images against 5.20 ms with full-length buffers); other
-// sizes and kernel gridding take the full-length one.
+// N = 1024 and 2048 take the column kernel that grids and exchanges through
+// half-length LDS buffers (N = 1024, natural weighting: 4.52 ms per 7,680 images
+// against 5.20 ms with full-length buffers, which cap it at 16 wavefronts per
+// CU); other sizes and kernel gridding take the full-length one. Below 1024 its
+// buffers do not limit the wavefronts, and columns of more than 128 entries,
+// which the half-length kernel loads twice, are loaded once: 1,280 uniform
+// images of 128^2 with 32,640 baselines 874 -> 461 us, 800 of 256^2 with 4,950
+// 228 -> 166 us, 1,000 of 512^2 with 6,786 382 -> 300 us.
 template <int N>
-constexpr bool cols_half() { return plan_even(N) && N <= 2048; }
+constexpr bool cols_half() { return N == 1024 || N == 2048; }
 
 template <int N, bool UNI>
 void launch_cols_image(ImgArgs& a, int n, int cpw, hipStream_t st) {
@@ -522,7 +526,15 @@ constexpr int ROWS_BLOCK_STORE_MAX_N = 1024;
 template <int N>
 constexpr bool rows_half() { return plan_even(N) && N <= 2048; }
 template <int N>
-constexpr size_t rows_lds_base() { return rows_half<N>() ? RowsHalf<N>::LDS : Rows<N>::LDS; }
+constexpr int row_pairs() {                  // per workgroup
+  if constexpr (rows_half<N>()) return RowsHalf<N>::PPW;
+  else return Rows<N>::PPW;
+}
+template <int N>
+constexpr size_t rows_lds_base() {
+  if constexpr (rows_half<N>()) return RowsHalf<N>::LDS;
+  else return Rows<N>::LDS;
+}
 
 template <int N, bool KB>
 void launch_rows(const blink_problem* p, ImgArgs& a, long long nwg, size_t lds, hipStream_t st) {
@@ -597,7 +609,7 @@ blink_status image_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t s
     }
     T_.end();
     // row pass: one workgroup per row tile, or a persistent grid of rows_wg workgroups
-    const long long row_tiles = (long long)n * cdiv(p->out_n / 2, Rows<N>::PPW);
+    const long long row_tiles = (long long)n * cdiv(p->out_n / 2, row_pairs<N>());
     const long long nwg = p->rows_wg > 0 ? std::min<long long>(row_tiles, p->rows_wg) : row_tiles;
     T_.begin(3);
     if (kb) launch_rows<N, true>(p, a, nwg, rows_lds, st);
@@ -682,7 +694,7 @@ blink_status adjoint_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t
       else
         hipLaunchKernelGGL((k_weights<N, false>), gw, dim3(Cols<N>::THREADS), ldsw, st, a);
     }
-    const dim3 g2(cdiv(p->out_n / 2, Rows<N>::PPW), n);
+    const dim3 g2(cdiv(p->out_n / 2, row_pairs<N>()), n);
     if constexpr (rows_half<N>())
       hipLaunchKernelGGL((k_rows_adj_half<N>), g2, dim3(RowsHalf<N>::THREADS), RowsHalf<N>::LDS, st, a);
     else
@@ -703,7 +715,7 @@ blink_status adjoint_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t
         hipLaunchKernelGGL((k_degrid_kb<N, KB_SMALL_SUPPORT>), gd, dim3(256), 0, st, a);
       else
         hipLaunchKernelGGL((k_degrid_kb<N, KB_MAX_SUPPORT>), gd, dim3(256), 0, st, a);
-    } else if constexpr (cols_half<N>()) {
+    } else if constexpr (rows_half<N>()) {
       if (uni) launch_cols_adj_half<N, true>(a, n, st);
       else launch_cols_adj_half<N, false>(a, n, st);
     } else if (uni) {

@@ -425,11 +425,10 @@ __host__ __device__ constexpr bool blocks_aligned(int n) {
   return plan_ok(n) && last_stage_ns(n) % WAVE == 0 && (n / pick_radix(n / last_stage_ns(n))) % WAVE == 0;
 }
 
-// Cutout store for blocks aligned to the wavefront width with hm a multiple
-// of it as well: each block is wholly kept or wholly dropped.
+// Cutout store with hm a multiple of the wavefront width, for blocks that lie
+// within 64 aligned positions: each block is wholly kept or wholly dropped.
 template <int N, int QB, class Store>
 __device__ __forceinline__ void cutout_block_aligned(unsigned lane, int hm, Store&& st) {
-  static_assert(QB % WAVE == 0, "block not aligned");
   if (QB < hm) st((unsigned)(QB + hm) + lane);
   else if (QB >= N - hm) st((unsigned)(QB - (N - hm)) + lane);
 }

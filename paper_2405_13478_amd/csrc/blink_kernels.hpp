@@ -1505,7 +1505,28 @@ __global__ void __launch_bounds__((Cols<N, CPW>::THREADS)) k_grid_cols(ImgArgs a
     a.kpart[(size_t)img * a.wstride + tile] = ks;
   }
 
-  if (MODE == MODE_IMAGE) {
+  if constexpr (MODE == MODE_IMAGE && plan_even(N) && N <= 256) {
+    // a column takes N / 16 lanes (one first-stage butterfly each), so the first
+    // wavefronts transform the tile's columns and the others are done; the
+    // exchanges use half of each column's buffer (2,000 images of 128^2 191 -> 161
+    // us, 800 of 256^2 166 -> 141; at 512^2, two columns a wavefront, 300 -> 328)
+    constexpr int L = N / 16, R = HalfIn<N, L>::R, PER = HalfIn<N, L>::PER;
+    const int vec = threadIdx.x / L, ln = threadIdx.x % L;
+    if (vec < CPW && c0 + vec < ncols) {
+      float2* b = lds + vec * C_::STRIDE;
+      HalfIn<N, L> x;
+#pragma unroll
+      for (int p = 0; p < PER; ++p)
+#pragma unroll
+        for (int r = 0; r < R; ++r) x.v[p][r] = b[pad(ln + p * L + r * (N / R))];
+      wave_sync();
+      float2* dst = a.half + ((size_t)li * H + c0 + vec) * a.M;
+      const int hm = a.M / 2;
+      wave_fft_half_emit<N, +1, 0, false, L>(b, ln, tw, x, [&](auto qb, float2 v) {
+        cutout_lane<N, decltype(qb)::value>(ln, hm, [&](unsigned m) { store_at(dst, m, v); });
+      });
+    }
+  } else if (MODE == MODE_IMAGE) {
     if (active) {
       // rows of the cutout straight from the last stage: output row m holds
       // v-frequency q = (m - M/2) mod N
@@ -1973,11 +1994,18 @@ __global__ void __launch_bounds__(Rows<N>::THREADS) k_rows(ImgArgs a) {
 // slice, each wavefront takes its first stage's lower inputs, then the upper
 // halves (z[N - k]) follow from the same registers. With no prefetch across
 // tiles and half the LDS, three workgroups share a CU instead of two.
+// Below N = 1024 a row pair takes N / 16 lanes (one first-stage butterfly each)
+// instead of a wavefront of which the others would idle, and a workgroup of 128
+// or 256 threads as many pairs: 2,000 images of 128^2 110 -> 40 us, 1,000 of
+// 512^2 -> 256^2 197 -> 136 us.
 template <int N>
 struct RowsHalf {
   static constexpr int STRIDE = padded_len(N / 2) + ((4 - padded_len(N / 2) % 32) + 32) % 32;
-  static constexpr int PPW = Rows<N>::PPW;
-  static constexpr int THREADS = PPW * WAVE;
+  static constexpr int L = N / 16 < WAVE ? N / 16 : WAVE;      // lanes per row pair
+  // at N = 2048 16 pairs, so that a column's slice is 256 contiguous bytes (128
+  // images of 2048^2 960 -> 930 us; at N = 1024 8 are better, 397 against 517)
+  static constexpr int THREADS = N == 2048 ? 1024 : N == 1024 ? 512 : N <= 256 ? 128 : 256;
+  static constexpr int PPW = THREADS / L;                      // row pairs per workgroup
   static constexpr int TW = TwLds<N>::ON ? tw_entries(N) : 0;
   static constexpr size_t LDS = (size_t)(PPW * STRIDE + TW) * sizeof(float2);
 };
@@ -1988,14 +2016,15 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
   static_assert(!AL || blocks_aligned(N), "aligned cutout needs aligned blocks");
   extern __shared__ float4 lds_raw[];
   constexpr int H = N / 2;
-  constexpr int PPW = RowsHalf<N>::PPW;
-  __shared__ int wred[PPW];                          // per-wavefront sums of the weight partials
+  constexpr int PPW = RowsHalf<N>::PPW, L = RowsHalf<N>::L;
+  constexpr int WAVES = RowsHalf<N>::THREADS / WAVE;
+  __shared__ int wred[WAVES];                        // per-wavefront sums of the weight partials
   constexpr int ST = RowsHalf<N>::STRIDE;
   constexpr int THR = RowsHalf<N>::THREADS;
   constexpr int EPT = (H * PPW + THR - 1) / THR;     // half-spectrum float4 loads per thread
-  constexpr int R0 = HalfIn<N>::R;
+  constexpr int R0 = HalfIn<N, L>::R;
   float2* lds = reinterpret_cast<float2*>(lds_raw);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = threadIdx.x % WAVE;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = threadIdx.x % L;
   const int M = a.M;
   const int npair = M / 2;
   const int ntr = (npair + PPW - 1) / PPW;           // row tiles per image
@@ -2011,6 +2040,7 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
     // they would stay live across the transforms and cost occupancy
     int lane_i = lane, ln = threadIdx.x;
     asm volatile("" : "+v"(lane_i), "+v"(ln));
+    const int vec = L == WAVE ? wave : ln / L;       // this lane's row pair of the tile
     // thread t serves pair slot t % PPW and columns t / PPW + i * (THR / PPW)
     const int kt = ln / PPW, pt = ln % PPW;
     const int li = tile / ntr, p0 = (tile % ntr) * PPW;
@@ -2043,10 +2073,10 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
         else wli += __shfl_xor(wli, o);
       }
       float2* zs = lds + pt * ST;                       // the packed row this thread fills
-      float2* z = lds + wave * ST;                      // the packed row this wavefront transforms
-      HalfIn<N> in;
+      float2* z = lds + vec * ST;                       // the packed row its lanes transform
+      HalfIn<N, L> in;
       __syncthreads();                                  // previous tile's rows have left LDS
-      if (lane_i == 0) wred[wave] = KB ? __float_as_int(wlf) : wli;
+      if (ln % WAVE == 0) wred[wave] = KB ? __float_as_int(wlf) : wli;
 #pragma unroll
       for (int i = 0; i < EPT; ++i) {                   // lower half: z[k] = A[k] + i B[k]
         const int k = kt + i * (THR / PPW);
@@ -2059,16 +2089,16 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
       float W;
       if (KB) {
         float f = 0.f;
-        for (int w = 0; w < PPW; ++w) f += __int_as_float(wred[w]);
+        for (int w = 0; w < WAVES; ++w) f += __int_as_float(wred[w]);
         W = f;
       } else {
         int n = 0;
-        for (int w = 0; w < PPW; ++w) n += wred[w];
+        for (int w = 0; w < WAVES; ++w) n += wred[w];
         W = (float)n;
       }
       const float scale = a.norm ? (W > 0 ? 1.0f / W : 0.0f) : 1.0f;
       if (p0 == 0 && ln == 0 && a.weight_sum) a.weight_sum[img] = W;
-      half_read<N, R0, 0, ZB>(z, lane_i, in.v);
+      half_read<N, R0, 0, ZB, L>(z, lane_i, in.v);
       __syncthreads();
 #pragma unroll
       for (int i = 0; i < EPT; ++i) {                   // upper half: z[N - k] = conj A[k] + i conj B[k]
@@ -2079,8 +2109,8 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
         }
       }
       __syncthreads();
-      half_read<N, R0, 1, ZB>(z, lane_i, in.v);
-      const int pair = p0 + wave;
+      half_read<N, R0, 1, ZB, L>(z, lane_i, in.v);
+      const int pair = p0 + vec;
       if (pair < npair) {
         float* r0 = a.images + ((size_t)img * M + 2 * pair) * M;
         float* r1 = r0 + M;
@@ -2094,7 +2124,7 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
         if constexpr (HMC == 0) asm volatile("" : "+s"(hm));
         // image columns of the cutout straight from the last stage: column l
         // holds u-frequency q = (l - M/2) mod N; row 2p is Re z, row 2p+1 is Im z
-        wave_fft_half_emit<N, +1, ZB>(z, lane_i, tw, in, [&](auto qb, float2 v) {
+        wave_fft_half_emit<N, +1, ZB, false, L>(z, lane_i, tw, in, [&](auto qb, float2 v) {
           auto st = [&](unsigned l) {
             const float cl = KB ? lcorr[l] : 1.0f;
             store_at(r0, l, v.x * s0 * cl);
@@ -2105,7 +2135,7 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
         });
       }
     };
-    if (HalfIn<N>::R == 16 && zero_band(N, nz) >= 4) body(ic<HalfIn<N>::R == 16 ? 4 : 0>{});
+    if (R0 == 16 && zero_band(N, nz) >= 4) body(ic<R0 == 16 ? 4 : 0>{});
     else body(ic<0>{});
   }
 }
@@ -3027,18 +3057,18 @@ __device__ __forceinline__ void put_vis_grad(const ImgArgs& a, int li, int img, 
 // x[q] = value(q') for the M cutout positions (q' = q + M/2 mod N < M), zero
 // elsewhere. ZB: the zero band of a cutout of at most N - ZB N/16 points, whose
 // inputs are not formed.
-template <int N, int ZB, class Value>
-__device__ __forceinline__ void cutout_inputs(HalfIn<N>& in, int lane, int M, Value&& value) {
-  constexpr int R = HalfIn<N>::R, PER = HalfIn<N>::PER;
+template <int N, int ZB, int L, class Value>
+__device__ __forceinline__ void cutout_inputs(HalfIn<N, L>& in, int lane, int M, Value&& value) {
+  constexpr int R = HalfIn<N, L>::R, PER = HalfIn<N, L>::PER;
   constexpr int zlo = R / 2 - ZB / 2, zhi = R / 2 + ZB / 2;
 #pragma unroll
   for (int p = 0; p < PER; ++p)
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if (r < zlo || r >= zhi) {
-        const int q = lane + p * WAVE + r * (N / R);
+        const int q = lane + p * L + r * (N / R);
         const int m = r < R / 2 ? q + M / 2 : q + M / 2 - N;        // position in the cutout
-        const bool in_cut = (N / R % WAVE == 0 || lane + p * WAVE < N / R) && m >= 0 && m < M;
+        const bool in_cut = (N / R % L == 0 || lane + p * L < N / R) && m >= 0 && m < M;
         in.v[p][r] = in_cut ? value(m) : make_float2(0.f, 0.f);
       }
 }
@@ -3055,12 +3085,14 @@ constexpr bool adj_band() { return HalfIn<N>::R == 16; }
 template <int N>
 __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_adj_half(ImgArgs a) {
   using R_ = RowsHalf<N>;
-  constexpr int H = N / 2, PPW = R_::PPW, ST = R_::STRIDE, THR = R_::THREADS;
+  constexpr int H = N / 2, PPW = R_::PPW, ST = R_::STRIDE, THR = R_::THREADS, L = R_::L;
   constexpr int EPT = (H * PPW + THR - 1) / THR;
-  constexpr int RL = pick_radix(N / last_stage_ns(N)), PL = (N / RL + WAVE - 1) / WAVE;
+  constexpr int RL = pick_radix(N / last_stage_ns(N)), PL = (N / RL + L - 1) / L;
   extern __shared__ float4 lds_raw[];
   float2* lds = reinterpret_cast<float2*>(lds_raw);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = threadIdx.x % WAVE;
+  const int lane = threadIdx.x % L;
+  // this lane's row pair of the tile
+  const int vec = L == WAVE ? __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE) : (int)(threadIdx.x / L);
   const int li = blockIdx.y;
   const int img = a.img0 + li;
   const int M = a.M;
@@ -3068,11 +3100,11 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_adj_half(ImgArgs 
   const int p0 = blockIdx.x * PPW;
   const int nz = min(H, a.ncz[img]);
   const float W = a.wsum_in ? a.wsum_in[img]
-                  : a.kw > 0 ? sum_partials_f(a.wpart, img, a.wstride, a.wtiles, lane)
-                             : (float)sum_partials(a.wpart, img, a.wstride, a.wtiles, lane);
+                  : a.kw > 0 ? sum_partials_f(a.wpart, img, a.wstride, a.wtiles, threadIdx.x % WAVE)
+                             : (float)sum_partials(a.wpart, img, a.wstride, a.wtiles, threadIdx.x % WAVE);
   const float scale = a.norm ? (W > 0 ? 1.0f / W : 0.0f) : 1.0f;
   const float2* tw = stage_twiddles<N>(lds + PPW * ST);
-  const int pair = min(p0 + wave, npair - 1);                  // (spare wavefronts repeat the last pair)
+  const int pair = min(p0 + vec, npair - 1);                   // (spare lanes repeat the last pair)
   const float* g0 = a.image_grad + ((size_t)img * M + 2 * pair) * M;
   const float* g1 = g0 + M;
   // with a gridding kernel the forward pass divided pixel (m, l) by
@@ -3083,17 +3115,17 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_adj_half(ImgArgs 
     s1 *= kb_inv_taper((double)(2 * pair + 1 - M / 2) / N, a);
   }
   if (TwLds<N>::ON) __syncthreads();                           // the twiddles
-  float2* z = lds + wave * ST;
+  float2* z = lds + vec * ST;
   float2 up[PL][RL / 2];                                       // the outputs from N / 2 on
   auto body = [&](auto zbc) {
     constexpr int ZB = decltype(zbc)::value;
-    HalfIn<N> in;
-    cutout_inputs<N, ZB>(in, lane, M, [&](int l) {
+    HalfIn<N, L> in;
+    cutout_inputs<N, ZB, L>(in, lane, M, [&](int l) {
       const float cl = a.kw > 0 ? kb_inv_taper((double)(l - M / 2) / N, a) : 1.0f;
       return make_float2(g0[l] * s0 * cl, g1[l] * s1 * cl);
     });
-    wave_fft_half_emit<N, -1, ZB>(z, lane, tw, in, [&](auto qb, float2 v) {
-      constexpr int QB = decltype(qb)::value, r = QB / (N / RL), p = QB % (N / RL) / WAVE;
+    wave_fft_half_emit<N, -1, ZB, false, L>(z, lane, tw, in, [&](auto qb, float2 v) {
+      constexpr int QB = decltype(qb)::value, r = QB / (N / RL), p = QB % (N / RL) / L;
       if constexpr (QB < H) z[pad(QB + lane)] = v;
       else up[p][r - RL / 2] = v;
     });
@@ -3113,9 +3145,9 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_adj_half(ImgArgs 
   __syncthreads();
 #pragma unroll
   for (int p = 0; p < PL; ++p)
-    if ((N / RL) % WAVE == 0 || lane + p * WAVE < N / RL)
+    if ((N / RL) % L == 0 || lane + p * L < N / RL)
 #pragma unroll
-      for (int r = 0; r < RL / 2; ++r) z[pad(p * WAVE + r * (N / RL) + lane)] = up[p][r];
+      for (int r = 0; r < RL / 2; ++r) z[pad(p * L + r * (N / RL) + lane)] = up[p][r];
   __syncthreads();
   float4* dst = reinterpret_cast<float4*>(a.half + (size_t)li * H * M);
 #pragma unroll
@@ -3176,7 +3208,7 @@ __global__ void __launch_bounds__((ColsHalf<N, CPW, UNI>::THREADS)) k_cols_adj_h
   auto body = [&](auto zbc) {
     constexpr int ZB = decltype(zbc)::value;
     HalfIn<N> in;
-    cutout_inputs<N, ZB>(in, lane, M, [&](int m) { return srcc[m]; });
+    cutout_inputs<N, ZB, WAVE>(in, lane, M, [&](int m) { return srcc[m]; });
     wave_fft_half_emit<N, -1, ZB, C_::CL>(buf, lane, tw, in, [&](auto qb, float2 v) {
       constexpr int QB = decltype(qb)::value, r = QB / (N / RL), p = QB % (N / RL) / WAVE;
       if constexpr (QB < H) buf[pad(QB + lane)] = v;
