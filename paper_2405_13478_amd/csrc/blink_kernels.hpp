@@ -895,11 +895,12 @@ __global__ void __launch_bounds__(256) k_vmax(const double* __restrict__ sv, con
 
 // Zero band of an image's column transforms (see zero_band): the rows beyond
 // rint(vmax |s|) are empty. Non-finite or out-of-range bounds give 0.
+// reach: rows that an entry touches beyond its nearest one.
 template <int N>
-__device__ __forceinline__ int column_zero_band(const ImgArgs& a, int t, double s) {
+__device__ __forceinline__ int column_zero_band(const ImgArgs& a, int t, double s, int reach = 0) {
   if (a.vmax == nullptr) return 0;
   const double vc = rint(a.vmax[t] * fabs(s));
-  return (vc >= 0.0 && vc < (double)(N / 2)) ? zero_band(N, (int)vc + 1) : 0;
+  return (vc >= 0.0 && vc < (double)(N / 2)) ? zero_band(N, (int)vc + 1 + reach) : 0;
 }
 
 // Sum of the per-tile partials of one image (read by one wavefront; every
@@ -1185,15 +1186,67 @@ __device__ __forceinline__ float kb_inv_taper(double xi, const ImgArgs& a) {
   return (float)(a.ktaper0_d / f);
 }
 
-// Adds w[k] v to rows j0 + k, k < nrow, of this column for every active
-// lane, with one claim per entry instead of one per row: lanes with the same
-// first row j0 take turns, lowest lane first (the claim protocol of
-// wave_add, keyed on j0), and lanes with different j0 never reach the same
-// row at the same k, so a turn adds all of its lanes' rows in sequence over
-// k. Each element receives its adds in a fixed order: step, turn, k.
+// Rows of a column under kernel gridding. Sizes whose transform starts from
+// registers (plan_even up to 2048) keep row j, -N/2 <= j < N/2, at j + N/2
+// without padding, so that a footprint is one run of addresses: one base per
+// entry and constant offsets, instead of a wrap and a padded index per row. The
+// others keep the transform's padded layout.
+template <int N>
+constexpr bool kb_signed() { return plan_even(N) && N <= 2048; }
+template <int N>
+__device__ __forceinline__ int kb_row(int r) {        // place of row r, 0 <= r < N
+  return kb_signed<N>() ? (r < N / 2 ? r + N / 2 : r - N / 2) : pad(r);
+}
+
+// Number of active lanes below this one with the same BITS-bit key: the lanes
+// that agree with it in every bit, from one ballot a bit.
+template <int BITS>
+__device__ __forceinline__ int rank_among_equal(int key, bool active) {
+  unsigned long long same = __ballot(active);
+#pragma unroll
+  for (int b = 0; b < BITS; ++b) {
+    const unsigned long long ones = __ballot((key >> b) & 1);
+    same &= ((key >> b) & 1) ? ones : ~ones;
+  }
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(same >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)same, 0u));
+}
+
+// Adds w[k] v to rows j0 + k, k < nrow, of this column for every active lane:
+// lanes with the same first row j0 take turns, lowest lane first, and lanes with
+// different j0 never reach the same row at the same k, so a turn adds all of its
+// lanes' rows in sequence over k. Each element receives its adds in a fixed
+// order: step, turn, k. In the signed layout a lane's turn is the number of lanes
+// below it with the same j0, from ballots (no LDS round trips before a turn, and
+// no waiting for lanes whose j0 only shares a claim slot); the other sizes claim
+// turns as wave_add does, keyed on j0. nrow is W or W + 1; with W rows the signed
+// layout adds w[W] = 0 to the row after them (there is one: the buffer is longer
+// than N).
+// What bounds it: the chain of W + 1 dependent read-modify-writes per turn at 16
+// wavefronts per CU (the buffers' LDS), and the weights. 384 images of 1024^2,
+// W = 6: the column launch 840 -> 679 us (736 with the layout alone, 697 with the
+// ballots, then the row offsets and the keep rule in fewer double operations).
 template <int N, bool COUNT, int KMAX, int SLOTS>
 __device__ __forceinline__ void kb_add_rows(float2* buf, int* cnt, int j0, int nrow, const float (&w)[KMAX + 1],
                                             float2 v, bool active, int kw, Claim<SLOTS>& cl, int lane) {
+  if constexpr (kb_signed<N>()) {
+    float2* row = buf + (j0 + N / 2);
+    constexpr int BITS = N >= 1024 ? 10 : N >= 512 ? 9 : N >= 256 ? 8 : 7;
+    const int below = rank_among_equal<BITS>(j0, active);
+    const int rank = active ? below : -1;
+    for (int t = 0; __ballot(rank >= t) != 0; ++t) {
+      if (rank == t) {
+#pragma unroll
+        for (int k = 0; k <= KMAX; ++k) {
+          if (k > kw) break;
+          const float2 d = row[k];
+          row[k] = make_float2(d.x + w[k] * v.x, d.y + w[k] * v.y);
+          if (COUNT && k < nrow) cnt[j0 + N / 2 + k] += 1;
+          wave_sync();
+        }
+      }
+    }
+    return;
+  }
   bool pending = active;
   while (__ballot(pending) != 0) {
     const unsigned tag = cl.turn * CLAIM_TAG + (unsigned)(CLAIM_TAG - lane);
@@ -1248,9 +1301,9 @@ __device__ __forceinline__ void grid_steps_kb(const ImgArgs& a, const ColSpan& s
       xv = a.sv[tb + j] * s;
       b = a.perm[tb + j];
     }
-    // kept iff the whole footprint lies inside |i| < N/2 on both axes
-    ok = ok && ceil(xu - hw) > (double)-H && floor(xu + hw) < (double)H &&
-         ceil(xv - hw) > (double)-H && floor(xv + hw) < (double)H;
+    // kept iff the whole footprint lies inside |i| < N/2 on both axes, that is
+    // ceil(x - W/2) > -N/2 and floor(x + W/2) < N/2
+    ok = ok && fabs(xu) + hw < (double)H && fabs(xv) + hw < (double)H;
     if (cj) { xu = -xu; xv = -xv; }
     const bool home = ok && rint(xu) == (double)c;
     kd += __popcll(__ballot(home && !cj));
@@ -1260,6 +1313,7 @@ __device__ __forceinline__ void grid_steps_kb(const ImgArgs& a, const ColSpan& s
     float2 v = make_float2(0.f, 0.f);
     float wu = 0.f;
     int j0 = 0, nrow = 0;
+    float dhi = 0.f, dlo = 0.f;
     if (in) {
       v = load_vis(a, vb + b, b, ch);
       if (a.sd != nullptr) v = rotate_phase(v, a.sd[tb + j], a.freq[ch]);
@@ -1269,6 +1323,11 @@ __device__ __forceinline__ void grid_steps_kb(const ImgArgs& a, const ColSpan& s
       if (dens != nullptr) wu = wu / (float)dens[j];
       j0 = (int)ceil(xv - hw);
       nrow = (int)floor(xv + hw) - j0 + 1;       // W or W + 1 rows
+      // j0 - x_v in two floats, the first a multiple of 2^-18, so that k + dhi
+      // is exact and (k + dhi) + dlo is the double j0 + k - x_v rounded once
+      const double d0 = (double)j0 - xv;
+      dhi = (float)(rint(d0 * 0x1p18) * 0x1p-18);
+      dlo = (float)(d0 - (double)dhi);
     }
     float w[KMAX + 1];
 #pragma unroll
@@ -1276,7 +1335,7 @@ __device__ __forceinline__ void grid_steps_kb(const ImgArgs& a, const ColSpan& s
       w[k] = 0.f;
       if (k > kw) break;
       if (k < nrow) {
-        w[k] = wu * kb_weight((float)((double)(j0 + k) - xv), a);
+        w[k] = wu * kb_weight(((float)k + dhi) + dlo, a);
         wsum += w[k];
       }
     }
@@ -1518,13 +1577,38 @@ __global__ void __launch_bounds__((Cols<N, CPW>::THREADS)) k_grid_cols(ImgArgs a
 #pragma unroll
       for (int p = 0; p < PER; ++p)
 #pragma unroll
-        for (int r = 0; r < R; ++r) x.v[p][r] = b[pad(ln + p * L + r * (N / R))];
+        for (int r = 0; r < R; ++r) {
+          const int q = ln + p * L + r * (N / R);
+          x.v[p][r] = b[KB ? kb_row<N>(q) : pad(q)];
+        }
       wave_sync();
       float2* dst = a.half + ((size_t)li * H + c0 + vec) * a.M;
       const int hm = a.M / 2;
       wave_fft_half_emit<N, +1, 0, false, L>(b, ln, tw, x, [&](auto qb, float2 v) {
         cutout_lane<N, decltype(qb)::value>(ln, hm, [&](unsigned m) { store_at(dst, m, v); });
       });
+    }
+  } else if constexpr (MODE == MODE_IMAGE && KB && kb_signed<N>()) {
+    if (active) {
+      float2* dst = a.half + ((size_t)li * H + col) * a.M;
+      const int hm = a.M / 2;
+      auto body = [&](auto zbc) {
+        constexpr int ZB = decltype(zbc)::value, R = HalfIn<N>::R, zlo = R / 2 - ZB / 2, zhi = R / 2 + ZB / 2;
+        HalfIn<N> x;
+#pragma unroll
+        for (int p = 0; p < HalfIn<N>::PER; ++p)
+#pragma unroll
+          for (int r = 0; r < R; ++r)
+            if ((r < zlo || r >= zhi) && (N / R % WAVE == 0 || lane + p * WAVE < N / R))
+              x.v[p][r] = buf[kb_row<N>(lane + p * WAVE + r * (N / R))];
+        wave_sync();
+        wave_fft_half_emit<N, +1, ZB>(buf, lane, tw, x, [&](auto qb, float2 v) {
+          cutout_block<N, decltype(qb)::value>(lane, hm, [&](unsigned m) { store_at(dst, m, v); });
+        });
+      };
+      // a footprint reaches (W + 1) / 2 rows beyond the nearest one
+      if (HalfIn<N>::R == 16 && column_zero_band<N>(a, t, s, (a.kw + 1) / 2) >= 4) body(ic<HalfIn<N>::R == 16 ? 4 : 0>{});
+      else body(ic<0>{});
     }
   } else if (MODE == MODE_IMAGE) {
     if (active) {
@@ -1543,8 +1627,8 @@ __global__ void __launch_bounds__((Cols<N, CPW>::THREADS)) k_grid_cols(ImgArgs a
     for (int e = threadIdx.x; e < N * CPW; e += blockDim.x) {
       const int r = e / CPW, w = e % CPW;
       if (c0 + w < N) {
-        g[(size_t)r * N + c0 + w] = lds[w * C_::STRIDE + pad(r)];
-        if (gc) gc[(size_t)r * N + c0 + w] = lcnt[w * N + r];
+        g[(size_t)r * N + c0 + w] = lds[w * C_::STRIDE + (KB ? kb_row<N>(r) : pad(r))];
+        if (gc) gc[(size_t)r * N + c0 + w] = lcnt[w * N + (KB && kb_signed<N>() ? kb_row<N>(r) : r)];
       }
     }
   }
