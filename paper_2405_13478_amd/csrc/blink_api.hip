@@ -446,7 +446,7 @@ ImgArgs make_args(const blink_problem* p, const blink_inputs* in, const Work& w)
 // per-entry cell occupancy for kernel gridding with uniform weighting
 template <int N>
 void launch_kb_density(const ImgArgs& a, int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_kb_density<N>, dim3((unsigned)n), dim3(DENS_WAVES * WAVE),
+  hipLaunchKernelGGL(k_kb_density<N>, dim3((unsigned)(cdiv(n, 8) * 8LL * dens_tiles<N>())), dim3(DENS_WAVES * WAVE),
                      (size_t)DENS_WAVES * N * sizeof(int), st, a);
 }
 
