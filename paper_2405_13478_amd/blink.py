@@ -116,27 +116,32 @@ def supported_n(n: int) -> bool:
 
 
 # ---------------------------------------------------------------- helpers
+# A small image takes the GPU about 20 us, so what the binding does per call
+# counts: addresses go as plain ints (ctypes converts them), the checks avoid
+# building device and size objects, and the current stream is asked for by
+# number: 29.5 -> 24 us per 128^2 image, back to back.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dev(t, name, dtype=None, shape=None):
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise ValueError(f"{name} must be a CUDA (HIP) tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:             # (a torch.Size is a tuple)
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     return t
 
 
 def _stream(stream):
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(code, what):
@@ -202,13 +207,16 @@ def tuning_for(grid_n, out_n, n_bl, weighting, vis_type, chunk_images=None, cols
     """Tunables for a shape: explicit values win, then the autotuner's cache, then 0 (defaults)."""
     from . import autotune
     t = autotune.lookup(grid_n, out_n, n_bl, weighting, vis_type) or {}
-    pick = lambda v, k: int(v) if v is not None else int(t.get(k, 0))
-    return dict(chunk_images=pick(chunk_images, "chunk_images"), cols_per_wg=pick(cols_per_wg, "cols_per_wg"),
-                rows_wg=pick(rows_wg, "rows_wg"))
+    return dict(chunk_images=int(t.get("chunk_images", 0) if chunk_images is None else chunk_images),
+                cols_per_wg=int(t.get("cols_per_wg", 0) if cols_per_wg is None else cols_per_wg),
+                rows_wg=int(t.get("rows_wg", 0) if rows_wg is None else rows_wg))
+
+
+_VIS_TYPES = {torch.complex64: VIS_C64, torch.float16: VIS_F16, torch.bfloat16: VIS_BF16}
 
 
 def _vis_type(vis):
-    return {torch.complex64: VIS_C64, torch.float16: VIS_F16, torch.bfloat16: VIS_BF16}.get(vis.dtype, -1)
+    return _VIS_TYPES.get(vis.dtype, -1)
 
 
 def image_batch(vis, uvw_m, freq_hz, *, grid_n, pixscale, out_n=None, weighting=NATURAL,
