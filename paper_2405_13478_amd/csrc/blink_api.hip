@@ -443,11 +443,19 @@ ImgArgs make_args(const blink_problem* p, const blink_inputs* in, const Work& w)
   return a;
 }
 
-// per-entry cell occupancy for kernel gridding with uniform weighting
+// per-entry cell occupancy for kernel gridding with uniform weighting; launches
+// of at most 2^31 threads (a chunk of many images with small cutouts has more)
 template <int N>
-void launch_kb_density(const ImgArgs& a, int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_kb_density<N>, dim3((unsigned)(cdiv(n, 8) * 8LL * dens_tiles<N>())), dim3(DENS_WAVES * WAVE),
-                     (size_t)DENS_WAVES * N * sizeof(int), st, a);
+void launch_kb_density(ImgArgs a, int n, hipStream_t st) {
+  constexpr int STEP = (1 << 23) / dens_tiles<N>() / 8 * 8;
+  for (int i0 = 0; i0 < n; i0 += STEP) {
+    a.nimg = std::min(STEP, n - i0);
+    const long long wgs = cdiv(a.nimg, 8) * 8LL * dens_tiles<N>();      // whole groups of 8 images
+    hipLaunchKernelGGL(k_kb_density<N>, dim3((unsigned)wgs), dim3(DENS_WAVES * WAVE),
+                       (size_t)DENS_WAVES * N * sizeof(int), st, a);
+    a.img0 += a.nimg;
+    a.kdens += (size_t)a.nimg * a.B;
+  }
 }
 
 template <int N, bool UNI, int CPW>

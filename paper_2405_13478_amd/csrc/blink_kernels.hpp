@@ -10,12 +10,13 @@
 // Per chunk of images (t, c):
 //   k_bounds  - for every signed u cell, the first sorted position at or beyond
 //               it (a scan of the sorted u list at this channel's scale).
-//   k_grid_cols<N, MODE> - one wavefront per u cell column: gathers the column's
-//               baselines (directly and as conjugates of the mirror column),
-//               accumulates sums (and counts) in LDS, applies the weighting,
-//               then either writes the grid column (MODE_GRID) or runs the
-//               inverse transform along v and writes the rows of the cutout
-//               (MODE_IMAGE) - the grid never reaches HBM on the image path.
+//   k_grid_cols / k_grid_cols_half - one wavefront per u cell column: gathers the
+//               column's baselines (directly and as conjugates of the mirror
+//               column), accumulates sums (and counts) in LDS, applies the
+//               weighting, then runs the inverse transform along v and writes
+//               the rows of the cutout - the grid never reaches HBM on the image
+//               path. k_grid_write (and MODE_GRID of k_grid_cols, with a gridding
+//               kernel) write the grid itself.
 //   k_rows<N> - two image rows per wavefront: Hermitian extension of the half
 //               spectrum (u cells 0..N/2-1), inverse transform along u, real
 //               part, FFT shift, 1/W and cutout fused into the store.
@@ -1047,12 +1048,15 @@ __device__ __forceinline__ void step_gather(const ImgArgs& a, int t, int ch, dou
 // wavefront writes, so the adds are done as plain read-modify-writes, and
 // lanes that would touch the same element take turns: each turn, every
 // pending lane posts a tag (turn * 64 + 64 - lane) to its key's claim slot
-// with an integer atomic max, and the lane whose tag survives adds its value. Lanes whose elements coincide share a
-// slot, so no two lanes of one turn touch one element; of the lanes sharing
+// with an integer atomic max, and the lane whose tag survives adds its value.
+// Lanes whose elements coincide share a slot, so no two lanes of one turn touch one element; of the lanes sharing
 // a slot the lowest goes first, so each element receives its adds in lane
 // order, step after step: the order of the sorted list, whatever the
 // grouping into steps. Tags grow with the wavefront's turn counter, so the
-// claim slots never need clearing after their initial zeroing.
+// claim slots never need clearing after their initial zeroing. Turns from ballots
+// (rank_among_equal, as the signed kernel rows take them) are no faster here, where
+// a turn is one add: all-sky columns 1,484 against 1,483 us, widefield 1,511
+// against 1,496.
 // Slots: a column buffer of up to 256 rows has one per row, so that only lanes
 // that really meet on a row wait for each other (2.7 instead of 4 turns a step
 // of the all-sky columns); for longer buffers the words would cost a workgroup
@@ -1439,8 +1443,8 @@ struct Cols {
 
 // One workgroup = CPW consecutive u-cell columns of one image; one wavefront
 // per column. MODE_IMAGE: columns 0..N/2-1 (the half spectrum), transform
-// along v, rows of the cutout written to `half`. MODE_GRID: all N columns,
-// weighted grid and counts written out.
+// along v, rows of the cutout written to `half`. MODE_GRID (kernel gridding): all
+// N columns, weighted grid and counts written out.
 // The 1D grid is laid out so that all column tiles of an image share one XCD
 // (workgroup L runs on XCD L mod 8): the image's visibility row and the
 // timestep's sorted lists are then fetched into a single L2.
@@ -1451,6 +1455,7 @@ struct Cols {
 template <int N, int MODE, bool UNI, int CPW = cols_per_wg(N), bool KB = false, int KMAX = 16>
 __global__ void __launch_bounds__((Cols<N, CPW>::THREADS)) k_grid_cols(ImgArgs a) {
   static_assert(!(KB && UNI), "kernel gridding weights uniformly through a.kdens");
+  static_assert(KB || MODE == MODE_IMAGE, "k_grid_write writes the nearest-cell grids");
   extern __shared__ float4 lds_raw[];
   __shared__ int red[2 * CPW];
   using C_ = Cols<N, CPW>;
@@ -1513,8 +1518,8 @@ __global__ void __launch_bounds__((Cols<N, CPW>::THREADS)) k_grid_cols(ImgArgs a
     wave_sync();
     // baselines counted once: the direct entry of every cell column, plus the
     // conjugate entries of columns whose mirror the image path never visits
-    kept_b = kd + ((MODE == MODE_IMAGE && cs > 0) ? kc : 0);
-    const int mult = (MODE == MODE_IMAGE && cs > 0) ? 2 : 1;
+    kept_b = kd + (cs > 0 ? kc : 0);
+    const int mult = cs > 0 ? 2 : 1;
     if (UNI) {
       int occ = 0;
       for (int r = lane; r < N; r += WAVE) {
@@ -1611,8 +1616,8 @@ __global__ void __launch_bounds__((Cols<N, CPW>::THREADS)) k_grid_cols(ImgArgs a
     for (int e = threadIdx.x; e < N * CPW; e += blockDim.x) {
       const int r = e / CPW, w = e % CPW;
       if (c0 + w < N) {
-        g[(size_t)r * N + c0 + w] = lds[w * C_::STRIDE + (KB ? kb_row<N>(r) : pad(r))];
-        if (gc) gc[(size_t)r * N + c0 + w] = lcnt[w * N + (KB && kb_signed<N>() ? kb_row<N>(r) : r)];
+        g[(size_t)r * N + c0 + w] = lds[w * C_::STRIDE + kb_row<N>(r)];
+        if (gc) gc[(size_t)r * N + c0 + w] = lcnt[w * N + (kb_signed<N>() ? kb_row<N>(r) : r)];
       }
     }
   }
@@ -1830,7 +1835,7 @@ __global__ void __launch_bounds__((ColsHalf<N, CPW, UNI>::THREADS)) k_grid_cols_
 // writes: 32 images of 1024^2 126 -> 97 us, 4.2 TB/s (146 us with 8 columns).
 template <int N>
 struct GridWr {
-  static constexpr int CPW = N <= 1024 ? 16 : N <= 2048 ? 8 : 4, THREADS = CPW * WAVE;
+  static constexpr int CPW = N <= 8 ? 8 : N <= 1024 ? 16 : N <= 2048 ? 8 : 4, THREADS = CPW * WAVE;
   static constexpr int STRIDE = padded_len(N / 2);
   static constexpr int SLOTS = claim_slots(N / 2);
   static constexpr size_t LDS = (size_t)CPW * (STRIDE * sizeof(float2) + (N / 2) * sizeof(int) + SLOTS * sizeof(unsigned));
