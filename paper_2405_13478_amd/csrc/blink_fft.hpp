@@ -375,6 +375,12 @@ __device__ __forceinline__ void store_at(T* base, unsigned i, T v) {
   *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + i * (unsigned)sizeof(T)) = v;
 }
 
+// base[i], addressed likewise.
+template <class T>
+__device__ __forceinline__ T load_at(const T* base, unsigned i) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + i * (unsigned)sizeof(T));
+}
+
 // Centred cutout of a length-N spectrum: frequency q goes to position q + hm
 // if q < hm, to q - (N - hm) if q >= N - hm, and is dropped otherwise (2 hm
 // kept points; output position hm holds frequency 0). For the block
