@@ -604,7 +604,12 @@ blink_status image_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t s
       using C_ = Cols<N, CPW>;
       a.ntiles = (int)cdiv(N / 2, CPW);
       const dim3 g1((unsigned)(cdiv(n, 8) * 8LL * a.ntiles));
-      if (p->kernel_support <= KB_SMALL_SUPPORT)
+      // M = N/2 with a short kernel, the usual case, has its cutout fixed at compile time
+      constexpr int HMC = half_cutout_form<N>() ? N / 4 : 0;
+      if (p->kernel_support <= KB_SMALL_SUPPORT && HMC > 0 && p->out_n == 2 * HMC)
+        hipLaunchKernelGGL((k_grid_cols<N, MODE_IMAGE, false, CPW, true, KB_SMALL_SUPPORT, HMC>), g1, dim3(C_::THREADS),
+                           C_::grid_lds_bytes(false), st, a);
+      else if (p->kernel_support <= KB_SMALL_SUPPORT)
         hipLaunchKernelGGL((k_grid_cols<N, MODE_IMAGE, false, CPW, true, KB_SMALL_SUPPORT>), g1, dim3(C_::THREADS),
                            C_::grid_lds_bytes(false), st, a);
       else

@@ -21,7 +21,8 @@ pytestmark = pytest.mark.gpu
     (12, 12, 8, 1, 2, 3, True, 0.15), (16, 16, 30, 1, 1, 4, True, 0.02), (32, 20, 40, 3, 3, 6, True, 0.2),
     (64, 32, 40, 1, 1, 16, False, 0.2), (64, 34, 90, 2, 1, 2, True, 0.15), (128, 128, 60, 1, 9, 2, True, 0.2),
     (180, 100, 30, 1, 1, 7, True, 0.2), (256, 100, 64, 1, 2, 9, False, 0.2), (512, 512, 30, 1, 1, 5, True, 0.002),
-    (1024, 512, 40, 1, 1, 8, True, 0.2), (2048, 64, 24, 1, 1, 6, True, 0.2)])
+    (1024, 512, 40, 1, 1, 8, True, 0.2), (1024, 510, 20, 1, 1, 3, False, 0.2), (2048, 64, 24, 1, 1, 6, True, 0.2),
+    (2048, 1024, 24, 1, 1, 4, False, 0.2)])
 def test_kernel_sizes(N, M, n_ant, T, C, W, uniform, sigma):
     rng = np.random.default_rng(N * 31 + W)
     B = n_ant * (n_ant - 1) // 2
