@@ -665,7 +665,7 @@ blink_status grid_n(const blink_problem* p, ImgArgs a, int chunk, hipStream_t st
 template <int N, bool UNI>
 void launch_cols_adj_half(ImgArgs& a, int n, hipStream_t st) {
   constexpr int CPW = N <= 1024 ? 8 : 4;
-  using C_ = ColsHalf<N, CPW, UNI>;
+  using C_ = ColsAdj<N, CPW, UNI>;
   a.ntiles = (int)cdiv(N / 2, CPW);
   hipLaunchKernelGGL((k_cols_adj_half<N, CPW, UNI>), dim3((unsigned)(cdiv(n, 8) * 8LL * a.ntiles)), dim3(C_::THREADS),
                      C_::LDS, st, a);

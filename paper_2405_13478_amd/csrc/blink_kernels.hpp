@@ -3264,9 +3264,21 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_adj_half(ImgArgs 
 // columns, in the entry's vis_grad slot.
 constexpr int GADJ = 4;
 
+// The twiddle table is the full one, every power rounded once from 64 bits. Formed
+// from the compact one, w^2k and w^3k carry the rounding of one and two FP32
+// products more: the gradients of 320 images of 1024^2 are then 1.39e-7 from 64
+// bits instead of 1.34e-7. Three workgroups of 8 columns share a CU either way.
 template <int N, int CPW, bool UNI>
-__global__ void __launch_bounds__((ColsHalf<N, CPW, UNI>::THREADS)) k_cols_adj_half(ImgArgs a) {
-  using C_ = ColsHalf<N, CPW, UNI>;
+struct ColsAdj {
+  static constexpr int STRIDE = padded_len(N / 2);
+  static constexpr int THREADS = CPW * WAVE;
+  static constexpr int TW = TwLds<N>::ON ? tw_entries(N) : 0;
+  static constexpr size_t LDS = (size_t)(CPW * STRIDE + TW) * sizeof(float2) + (UNI ? (size_t)CPW * (N / 2) * sizeof(int) : 0);
+};
+
+template <int N, int CPW, bool UNI>
+__global__ void __launch_bounds__((ColsAdj<N, CPW, UNI>::THREADS)) k_cols_adj_half(ImgArgs a) {
+  using C_ = ColsAdj<N, CPW, UNI>;
   constexpr int H = N / 2;
   constexpr int RL = pick_radix(N / last_stage_ns(N)), PL = (N / RL + WAVE - 1) / WAVE;
   extern __shared__ float4 lds_raw[];
@@ -3288,7 +3300,7 @@ __global__ void __launch_bounds__((ColsHalf<N, CPW, UNI>::THREADS)) k_cols_adj_h
   int* cnt = UNI ? reinterpret_cast<int*>(ltw + C_::TW) + wave * H : nullptr;
   const double s = cells_per_metre(a.freq[ch], a.ndx);
   const int M = a.M;
-  const float2* tw = stage_twiddles<N, C_::CL>(ltw);
+  const float2* tw = stage_twiddles<N>(ltw);
   if (TwLds<N>::ON) __syncthreads();
   if (cs >= nz) return;
   const float2* srcc = a.half + ((size_t)li * H + cs) * M;
@@ -3297,7 +3309,7 @@ __global__ void __launch_bounds__((ColsHalf<N, CPW, UNI>::THREADS)) k_cols_adj_h
     constexpr int ZB = decltype(zbc)::value;
     HalfIn<N> in;
     cutout_inputs<N, ZB, WAVE>(in, lane, M, [&](int m) { return srcc[m]; });
-    wave_fft_half_emit<N, -1, ZB, C_::CL>(buf, lane, tw, in, [&](auto qb, float2 v) {
+    wave_fft_half_emit<N, -1, ZB>(buf, lane, tw, in, [&](auto qb, float2 v) {
       constexpr int QB = decltype(qb)::value, r = QB / (N / RL), p = QB % (N / RL) / WAVE;
       if constexpr (QB < H) buf[pad(QB + lane)] = v;
       else up[p][r - RL / 2] = v;
