@@ -1202,6 +1202,18 @@ __device__ __forceinline__ int kb_row(int r) {        // place of row r, 0 <= r 
   return kb_signed<N>() ? (r < N / 2 ? r + N / 2 : r - N / 2) : pad(r);
 }
 
+// Whether the footprint of a baseline at cell position (xu, xv), each a product
+// rounded to double, lies inside |i| < N/2 (H = N/2) on both axes, that is
+// ceil(x - W/2) > -N/2 and floor(x + W/2) < N/2. The gridding, the occupancy pass
+// and the adjoint ask here: where one of them formed x +- W/2 in one rounding
+// (W >= N/2), the adjoint kept a baseline that the others had dropped, and divided
+// by an occupancy that nothing had written.
+template <int H>
+__device__ __forceinline__ bool kb_kept(double xu, double xv, double hw) {
+#pragma clang fp contract(off)
+  return fabs(xu) + hw < (double)H && fabs(xv) + hw < (double)H;
+}
+
 // Number of active lanes below this one with the same BITS-bit key: the lanes
 // that agree with it in every bit, from one ballot a bit.
 template <int BITS>
@@ -1306,9 +1318,7 @@ __device__ __forceinline__ void grid_steps_kb(const ImgArgs& a, const ColSpan& s
       xv = a.sv[tb + j] * s;
       b = a.perm[tb + j];
     }
-    // kept iff the whole footprint lies inside |i| < N/2 on both axes, that is
-    // ceil(x - W/2) > -N/2 and floor(x + W/2) < N/2
-    ok = ok && fabs(xu) + hw < (double)H && fabs(xv) + hw < (double)H;
+    ok = ok && kb_kept<H>(xu, xv, hw);
     if (cj) { xu = -xu; xv = -xv; }
     const bool home = ok && rint(xu) == (double)c;
     kd += __popcll(__ballot(home && !cj));
@@ -1392,7 +1402,7 @@ __global__ void __launch_bounds__(DENS_WAVES * WAVE) k_kb_density(ImgArgs a) {
   // nearest row of entry j (mirrored with mj), or N when it is not kept
   auto row_of = [&](int j, bool mj) -> int {
     const double xu = su[j] * s, xv = sv[j] * s;
-    if (!(fabs(xu) + hw < (double)H && fabs(xv) + hw < (double)H)) return N;
+    if (!kb_kept<H>(xu, xv, hw)) return N;
     const int r = (int)rint(xv);
     return mj ? -r : r;
   };
@@ -3447,9 +3457,7 @@ __global__ void __launch_bounds__(256) k_degrid_kb(ImgArgs a) {
   const double s = cells_per_metre(a.freq[ch], a.ndx);
   const double hw = 0.5 * a.kw;
   const double xu = a.su[tb + j] * s, xv = a.sv[tb + j] * s;
-  if (!(ceil(xu - hw) > (double)-H && floor(xu + hw) < (double)H && ceil(xv - hw) > (double)-H &&
-        floor(xv + hw) < (double)H))
-    return;                                          // not kept: its gradient stays zero
+  if (!kb_kept<H>(xu, xv, hw)) return;               // its gradient stays zero
   const int i0 = (int)ceil(xu - hw), ni = (int)floor(xu + hw) - i0 + 1;
   const int j0 = (int)ceil(xv - hw), nj = (int)floor(xv + hw) - j0 + 1;
   float wv[KMAX + 1];
