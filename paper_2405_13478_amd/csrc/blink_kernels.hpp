@@ -1234,9 +1234,9 @@ __device__ __forceinline__ int rank_among_equal(int key, bool active) {
 // order: step, turn, k. In the signed layout a lane's turn is the number of lanes
 // below it with the same j0, from ballots (no LDS round trips before a turn, and
 // no waiting for lanes whose j0 only shares a claim slot); the other sizes claim
-// turns as wave_add does, keyed on j0. nrow is W or W + 1; with W rows the signed
-// layout writes the row after them back as it was (there is one: the buffer is
-// longer than N), for 0 x v would spread an infinite or NaN visibility to it.
+// turns as wave_add does, keyed on j0. nrow is W or W + 1; in the signed layout the
+// few lanes with W + 1 add the last one apart (added to all with weight 0, it would
+// spread an infinite or NaN visibility to the row after the footprint).
 // What bounds it: the chain of W + 1 dependent read-modify-writes per turn at 16
 // wavefronts per CU (the buffers' LDS), and the weights. 384 images of 1024^2,
 // W = 6: the column launch 840 -> 679 us (736 with the layout alone, 697 with the
@@ -1252,14 +1252,23 @@ __device__ __forceinline__ void kb_add_rows(float2* buf, int* cnt, int j0, int n
     for (int t = 0; __ballot(rank >= t) != 0; ++t) {
       if (rank == t) {
 #pragma unroll
-        for (int k = 0; k <= KMAX; ++k) {
-          if (k > kw) break;
+        for (int k = 0; k < KMAX; ++k) {
+          if (k >= kw) break;
           const float2 d = row[k];
-          const float2 s = make_float2(d.x + w[k] * v.x, d.y + w[k] * v.y);
-          row[k] = k < nrow ? s : d;
-          if (COUNT && k < nrow) cnt[j0 + N / 2 + k] += 1;
+          row[k] = make_float2(d.x + w[k] * v.x, d.y + w[k] * v.y);
+          if (COUNT) cnt[j0 + N / 2 + k] += 1;
           wave_sync();
         }
+        if (nrow > kw) {                               // the few footprints of W + 1 rows
+          float wl = 0.f;
+#pragma unroll
+          for (int k = 0; k <= KMAX; ++k)
+            if (k == kw) wl = w[k];
+          const float2 d = row[kw];
+          row[kw] = make_float2(d.x + wl * v.x, d.y + wl * v.y);
+          if (COUNT) cnt[j0 + N / 2 + kw] += 1;
+        }
+        wave_sync();
       }
     }
     return;
