@@ -92,8 +92,9 @@ struct SortArgs {
 __device__ __forceinline__ void plane_uv(const SortArgs& a, size_t o, double& u, double& v) {
   const double* b = a.uvw + o * 3;
   if (a.proj) {
-    u = a.eu[0] * b[0] + a.eu[1] * b[1] + a.eu[2] * b[2];
-    v = a.ev[0] * b[0] + a.ev[1] * b[1] + a.ev[2] * b[2];
+    // written out, so that every caller has the same bits (the sort forms u again)
+    u = fma(a.eu[2], b[2], fma(a.eu[0], b[0], a.eu[1] * b[1]));
+    v = fma(a.ev[2], b[2], fma(a.ev[0], b[0], a.ev[1] * b[1]));
   } else {
     u = b[0];
     v = b[1];
@@ -198,10 +199,16 @@ __device__ __forceinline__ int nonempty_columns(int cfirst, int clast, int nv, i
 //      finds the range of the usable u, their number and the largest |v|;
 //   2. u is mapped linearly onto nb buckets. Subtraction, product and
 //      truncation never decrease with u, so the buckets are in order of u.
-//      Their counts are LDS integer atomics (two 16-bit counts a word), and the
-//      count returned is the baseline's slot in its bucket;
-//   3. a scan gives each bucket its first sorted position;
-//   4. the keys and indices go to their buckets in LDS;
+//      Their counts are LDS integer atomics (two 16-bit counts a word), and up to
+//      8 baselines a thread keep the count returned as their slot in the bucket;
+//   3. a scan turns the counts into each bucket's first sorted position (with 32
+//      baselines a thread, its end). Where a bucket has more than SORT_UNEVEN
+//      entries (a long baseline beside a dense core, a regular array whose
+//      baselines share a few u), 2 and 3 are done again with buckets between
+//      THREADS samples of the list, sorted as (key, index) pairs, so that they
+//      divide equal u too;
+//   4. the keys and indices go to their buckets in LDS, with 32 baselines a
+//      thread each bucket from its end down, which leaves its start in the table;
 //   5. an entry's position is its bucket's start plus the number of smaller
 //      (key, index) pairs in the bucket (about one entry a bucket when u is
 //      spread evenly; a centrally condensed array fills some with ten). Buckets
@@ -209,24 +216,33 @@ __device__ __forceinline__ int nonempty_columns(int cfirst, int clast, int nv, i
 //      the whole workgroup;
 //   6. u, v, index and delay are written in order (index_only: the index
 //      alone, see k_sort_gather).
+// Where all usable u are equal (a linear array), the order is that of the indices.
 // The positions are taken in `shares` parts, whole buckets each: as many as
 // fit in LDS, walked by one workgroup per timestep, or by gridDim.x of them
 // that each repeat 1-3.
-// A share that does not fit in LDS (a long list with most of it in one bucket)
-// is ordered by a stable radix sort of the keys instead, four bits a pass,
-// skipping digits that all keys share.
+// A share that does not fit in LDS even so (the samples missed where most of a
+// long list lies) is ordered by a stable radix sort of the keys instead, four
+// bits a pass, skipping digits that all keys share.
 // What bounds it: the latency of one workgroup (loads, barriers, LDS atomics),
-// not bandwidth; with many long lists the reads of uvw. Measured against the
-// networks and merges before it (whole order, largest |v| included): 496
-// baselines 24 -> 8 us, 8,128 baselines 130 -> 15 us, 32,640 baselines 185 ->
-// 45 us for one timestep and 900 -> 273 us for 200.
+// not bandwidth; with many long lists the reads of uvw. With 32 baselines a
+// thread only their buckets are kept between the steps, two a register (those
+// between samples wait in idx[0], which every workgroup of a timestep fills alike):
+// with the slots, 45 registers spilled to memory.
+// Measured against the networks and merges before it (order, largest |v|, bounds),
+// us for one timestep and for 200: 1,000 baselines 30 -> 14 and 32 -> 15; 8,128
+// baselines 131 -> 20 and 152 -> 46; 32,640 baselines 188 -> 50 and 877 -> 207. With
+// one far baseline, where linear buckets alone took 144 and 169 for 8,128 baselines
+// and 481 and 1,718 for 32,640: 51, 92, 162 and 501. At 51 different u: 52, 105, 183
+// and 667 (linear buckets alone 52, 140, 191 and 1,584).
 constexpr int SORT_ONE = 32768;          // largest list of this kernel (16-bit positions)
 constexpr int SORT_LIGHT = 128;          // larger buckets are sorted, not ranked by counting
-constexpr int SORT_WAVE_MAX = 2048;      // larger ones by the whole workgroup
-constexpr int SORT_SHARE = 10752;        // entries of a share that fit in LDS beside the bucket starts
+constexpr int SORT_UNEVEN = 256;         // a larger bucket asks for sampled ones
+constexpr int SORT_WAVE_MAX = 2048;      // larger ones are sorted by the whole workgroup
+constexpr int SORT_SHARE = 10752;        // entries of a share that fit in LDS beside the bucket ends
+constexpr int SORT_SHARES = 8;           // parts of a list
 constexpr int SORT_RADIX = 16;           // digits of the radix passes
 
-// Workgroup shapes: lists of up to 2,048 baselines take 256 threads (eight such
+// Workgroup shapes: lists of up to 1,024 baselines take 256 threads (eight such
 // workgroups share a CU), longer ones 1,024.
 template <int THREADS>
 struct SortWg {
@@ -243,9 +259,13 @@ struct SortWg {
     const size_t radix = (size_t)((n + 7) & ~7) * 2 + (size_t)SORT_RADIX * THREADS * 2;
     return n > SORT_SHARE && radix > list ? radix : list;
   }
-  __host__ __device__ static constexpr size_t lds_bytes(int n) {
-    return list_bytes(n) + (size_t)(buckets(n) / 2 + 1) * 4;
+  // starts or ends of the buckets (one more than buckets), and beside those of 2 THREADS buckets the samples
+  static constexpr int SAMPLES_AT = THREADS + 4;                     // in words
+  __host__ __device__ static constexpr size_t table_bytes(int n) {
+    const size_t linear = (size_t)(buckets(n) / 2 + 1) * 4, sampled = (size_t)SAMPLES_AT * 4 + (size_t)THREADS * 10;
+    return linear > sampled ? linear : sampled;
   }
+  __host__ __device__ static constexpr size_t lds_bytes(int n) { return list_bytes(n) + table_bytes(n); }
 };
 
 // Exclusive scan of one value per thread over the workgroup; `tot` is one word
@@ -329,17 +349,19 @@ __device__ __forceinline__ void radix_order(const SortArgs& a, size_t tb, unsign
   for (int sh = 0; sh < 64; sh += 4) {
     if (((diff >> sh) & (SORT_RADIX - 1)) == 0ull) continue;         // one digit for all: no change
     for (int d = 0; d < SORT_RADIX; ++d) cnt[d * THREADS + tid] = 0;
-    unsigned short id[PER];
-    unsigned char dg[PER];
+    unsigned id[PER / 2];                                            // two indices a word
+    auto digit_of = [&](int i) { return (int)((baseline_key(a, tb, i) >> sh) & (SORT_RADIX - 1)); };
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int j = tid * per + k;
+      int i = 0;
       if (k < per && j < B) {
-        id[k] = perm[j];
-        dg[k] = (unsigned char)((baseline_key(a, tb, id[k]) >> sh) & (SORT_RADIX - 1));
-        ++cnt[dg[k] * THREADS + tid];
+        i = perm[j];
+        ++cnt[digit_of(i) * THREADS + tid];
       }
-      if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);             // bounds the loads in flight
+      if (k % 2 == 0) id[k / 2] = (unsigned)i;
+      else id[k / 2] |= (unsigned)i << 16;
+      __builtin_amdgcn_sched_barrier(0);                             // bounds the loads in flight
     }
     __syncthreads();
     // exclusive scan in (digit, thread) order: SORT_RADIX consecutive counts a thread
@@ -355,10 +377,44 @@ __device__ __forceinline__ void radix_order(const SortArgs& a, size_t tb, unsign
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       const int j = tid * per + k;
-      if (k < per && j < B) perm[cnt[dg[k] * THREADS + tid]++] = id[k];
+      const int i = (int)((id[k / 2] >> (k % 2 * 16)) & 0xffffu);
+      if (k < per && j < B) perm[cnt[digit_of(i) * THREADS + tid]++] = (unsigned short)i;
+      __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
   }
+}
+
+// THREADS (key, index) pairs, one a thread, in ascending order into key, id (LDS):
+// a bitonic network, by shuffles where the partner is in the wavefront.
+template <int THREADS>
+__device__ __forceinline__ void sort_samples(unsigned long long k, int i, unsigned long long* key, unsigned short* id) {
+  const int tid = threadIdx.x;
+#pragma unroll 1
+  for (int run = 2; run <= THREADS; run *= 2) {
+#pragma unroll 1
+    for (int d = run / 2; d > 0; d /= 2) {
+      unsigned long long ko;
+      int io;
+      if (d < WAVE) {
+        ko = __shfl_xor(k, d);
+        io = __shfl_xor(i, d);
+      } else {
+        key[tid] = k;
+        id[tid] = (unsigned short)i;
+        __syncthreads();
+        ko = key[tid ^ d];
+        io = id[tid ^ d];
+        __syncthreads();
+      }
+      const bool less = ko < k || (ko == k && io < i);
+      const bool low = ((tid & run) == 0) == ((tid & d) == 0);        // keeps the smaller of the two
+      if (less == low) { k = ko; i = io; }
+    }
+  }
+  key[tid] = k;
+  id[tid] = (unsigned short)i;
+  __syncthreads();
 }
 
 template <int THREADS, int PER, bool BOUNDS>
@@ -368,10 +424,14 @@ __global__ void __launch_bounds__(THREADS) k_sort_one(SortArgs a, int shares, in
   constexpr int WAVES = THREADS / WAVE;
   constexpr int MAX_HEAVY = SORT_SHARE / SORT_LIGHT + 1;
   extern __shared__ float4 lds_raw[];
-  __shared__ double s_red[3][WAVES];
+  __shared__ unsigned long long s_key[2][WAVES];
+  __shared__ double s_vm[WAVES];
   __shared__ int s_cnt[2][WAVES];
   __shared__ unsigned s_tot[WAVES];
-  __shared__ int s_p0, s_p1, s_ps, s_heavy;
+  // per share: the positions [p0, p1) it writes, the start ps of the bucket before
+  // p0, that bucket b0 and the last one b1
+  __shared__ int s_p0[SORT_SHARES], s_p1[SORT_SHARES], s_ps[SORT_SHARES], s_b0[SORT_SHARES], s_b1[SORT_SHARES];
+  __shared__ int s_heavy;
   __shared__ unsigned s_big;
   __shared__ unsigned s_list[MAX_HEAVY];             // heavy buckets: start << 16 | size
   __shared__ unsigned long long s_diff;
@@ -383,41 +443,55 @@ __global__ void __launch_bounds__(THREADS) k_sort_one(SortArgs a, int shares, in
   unsigned long long* keys = reinterpret_cast<unsigned long long*>(lds_raw);
   unsigned short* ids = reinterpret_cast<unsigned short*>(keys + cap);
   unsigned short* ord = ids + cap;
-  unsigned* hist = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds_raw) + W_::list_bytes(B));
-  const int nb = W_::buckets(B), wpt = nb / 2 / THREADS;             // buckets; words of two counts a thread
+  unsigned* table = reinterpret_cast<unsigned*>(reinterpret_cast<char*>(lds_raw) + W_::list_bytes(B));
+  unsigned long long* skey = reinterpret_cast<unsigned long long*>(table + W_::SAMPLES_AT);
+  unsigned short* sid = reinterpret_cast<unsigned short*>(skey + THREADS);
+  int nb = W_::buckets(B);
 
-  // 1. load and reduce. Up to 8 baselines a thread stay in registers; of 32
-  // they would spill, so u is read again: from uvw, or (index_only, where su is
-  // not yet written) from a packed copy in su.
+  // 1. load and reduce. Up to 8 baselines a thread keep their u in registers; of
+  // 32, u is read again: from uvw, or (index_only, where su is not yet written)
+  // from a packed copy in su.
   constexpr bool KEEP = PER <= 8;
-  double u[KEEP ? PER : 1];
-  unsigned okm = 0;
-  double umin = __builtin_inf(), umax = -__builtin_inf(), vm = 0.0;
-  int unf = 0;
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    int i = k * THREADS + tid;
-    asm volatile("" : "+v"(i));                                      // its address is formed here, not kept
-    double uk = 0.0;
-    if (i < B) {
-      double v;
-      plane_uv(a, tb + i, uk, v);
-      const bool flagged = a.flags != nullptr && a.flags[tb + i] != 0;
-      unf += flagged ? 0 : 1;
-      if (!flagged && isfinite(uk) && isfinite(v)) {
-        okm |= 1u << k;
-        umin = fmin(umin, uk);
-        umax = fmax(umax, uk);
-        vm = fmax(vm, fabs(v));
-      }
-      if (!KEEP && index_only) a.su[tb + i] = uk;
-    }
-    if constexpr (KEEP) u[k] = uk;
-    if (k % 8 == 7) __builtin_amdgcn_sched_barrier(0);               // loads in flight
-  }
-  auto u_of = [&](int k, int i) -> double {                          // u of baseline i, the thread's k-th
-    if constexpr (KEEP) return u[k];
+  constexpr int BATCH = PER < 8 ? PER : 8;                            // baselines at once
+  // the thread's number, opaque: what follows from it is formed where it is used
+  // (kept across the steps, baseline numbers and addresses spill)
+  auto thread = [&]() -> int {
+    int i = tid;
     asm volatile("" : "+v"(i));
+    return i;
+  };
+  double u[KEEP ? PER : 1];
+  unsigned bs[KEEP ? PER : PER / 2];                                 // bucket and slot << 16, or two buckets
+  unsigned okm = 0;
+  unsigned long long kmin = KEY_MAX, kmax = 0ull;                    // keys, which tell 0 from -0
+  double vm = 0.0;
+  int unf = 0;
+#pragma unroll 1
+  for (int k0 = 0; k0 < PER; k0 += BATCH) {
+#pragma unroll
+    for (int e = 0; e < BATCH; ++e) {
+      const int i = (k0 + e) * THREADS + thread();
+      double uk = 0.0;
+      if (i < B) {
+        double v;
+        plane_uv(a, tb + i, uk, v);
+        const bool flagged = a.flags != nullptr && a.flags[tb + i] != 0;
+        unf += flagged ? 0 : 1;
+        if (!flagged && isfinite(uk) && isfinite(v)) {
+          okm |= 1u << (k0 + e);
+          const unsigned long long k = order_key(uk);
+          kmin = min(kmin, k);
+          kmax = max(kmax, k);
+          vm = fmax(vm, fabs(v));
+        }
+        if (!KEEP && index_only) a.su[tb + i] = uk;
+      }
+      if constexpr (KEEP) u[e] = uk;
+    }
+  }
+  auto u_of = [&](int k0, int e) -> double {                         // u of the thread's baseline k0 + e
+    if constexpr (KEEP) return u[e];
+    const int i = (k0 + e) * THREADS + thread();
     double uk = 0.0, vk;
     if (i < B) {
       if (index_only) uk = a.su[tb + i];
@@ -425,79 +499,143 @@ __global__ void __launch_bounds__(THREADS) k_sort_one(SortArgs a, int shares, in
     }
     return uk;
   };
-  for (int w = tid; w <= nb / 2; w += THREADS) hist[w] = 0u;
+  for (int w = tid; w <= nb / 2; w += THREADS) table[w] = 0u;
   int val = __popc(okm);
   for (int o = WAVE / 2; o > 0; o >>= 1) {
-    umin = fmin(umin, __shfl_xor(umin, o));
-    umax = fmax(umax, __shfl_xor(umax, o));
+    kmin = min(kmin, __shfl_xor(kmin, o));
+    kmax = max(kmax, __shfl_xor(kmax, o));
     vm = fmax(vm, __shfl_xor(vm, o));
     unf += __shfl_xor(unf, o);
     val += __shfl_xor(val, o);
   }
   if (lane == 0) {
-    s_red[0][wave] = umin; s_red[1][wave] = umax; s_red[2][wave] = vm;
+    s_key[0][wave] = kmin; s_key[1][wave] = kmax; s_vm[wave] = vm;
     s_cnt[0][wave] = unf; s_cnt[1][wave] = val;
   }
   if (tid == 0) s_big = 0u;
   __syncthreads();
   {
     const int w = lane % WAVES;
-    umin = s_red[0][w]; umax = s_red[1][w]; vm = s_red[2][w];
+    kmin = s_key[0][w]; kmax = s_key[1][w]; vm = s_vm[w];
     unf = s_cnt[0][w]; val = s_cnt[1][w];
     for (int o = WAVES / 2; o > 0; o >>= 1) {
-      umin = fmin(umin, __shfl_xor(umin, o));
-      umax = fmax(umax, __shfl_xor(umax, o));
+      kmin = min(kmin, __shfl_xor(kmin, o));
+      kmax = max(kmax, __shfl_xor(kmax, o));
       vm = fmax(vm, __shfl_xor(vm, o));
       unf += __shfl_xor(unf, o);
       val += __shfl_xor(val, o);
     }
   }
-  const int nv = val;
+  // (the same in every lane: scalar registers)
+  auto scalar = [](unsigned long long v) {
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return ((unsigned long long)hi << 32) | (unsigned)__builtin_amdgcn_readfirstlane((unsigned)v);
+  };
+  kmin = scalar(kmin);
+  kmax = scalar(kmax);
+  const double umin = key_value(kmin), umax = key_value(kmax);       // (of no use when nothing is usable)
+  const int nv = __builtin_amdgcn_readfirstlane(val);
   if (g == 0 && tid == 0) {
     a.n_unflagged[t] = unf;
     a.n_valid[t] = nv;
     if (a.vmax != nullptr) a.vmax[t] = vm;
   }
 
-  // 2. buckets and slots (a degenerate range puts all into one bucket)
+  // 2. buckets (a degenerate range puts all into one)
   double scale = (double)nb / (umax - umin);
   if (!(umax > umin) || !isfinite(scale)) scale = 0.0;
-  auto bucket_of = [&](double x) -> unsigned {                        // (unusable ones: any bucket)
+  scale = __longlong_as_double((long long)scalar((unsigned long long)__double_as_longlong(scale)));
+  auto linear = [&](double x) -> unsigned {                          // (unusable ones: any bucket)
     return (unsigned)fmin(fmax((x - umin) * scale, 0.0), (double)(nb - 1));
   };
-  unsigned bs[PER];                                                  // bucket and slot << 16
-  constexpr int BATCH = PER < 8 ? PER : 8;                            // LDS round trips in flight
+  // with samples: how many of samples 1 .. THREADS - 1 are not above (u, index), of
+  // the thread's baselines i0, i0 + THREADS, ..
+  auto between = [&](const double (&x)[BATCH], int i0, unsigned (&b)[BATCH]) {
+    constexpr int U = BATCH < 4 ? BATCH : 4;                         // searches at once
 #pragma unroll
-  for (int k0 = 0; k0 < PER; k0 += BATCH) {
-    unsigned old[BATCH];
-    double uk[BATCH];
+    for (int q = 0; q < BATCH; q += U) {
+      unsigned long long k[U];
+      unsigned bq[U];
 #pragma unroll
-    for (int e = 0; e < BATCH; ++e) uk[e] = u_of(k0 + e, (k0 + e) * THREADS + tid);
+      for (int e = 0; e < U; ++e) { k[e] = order_key(x[q + e]); bq[e] = 0u; }
+#pragma unroll 1
+      for (int h = THREADS / 2; h > 0; h /= 2) {
+        unsigned long long ks[U];
 #pragma unroll
-    for (int e = 0; e < BATCH; ++e) {
-      const int k = k0 + e;
-      bs[k] = bucket_of(uk[e]);
-      old[e] = 0u;
-      if ((okm >> k) & 1u) old[e] = atomicAdd(&hist[bs[k] >> 1], 1u << ((bs[k] & 1u) * 16u));
+        for (int e = 0; e < U; ++e) ks[e] = skey[bq[e] + h];
+#pragma unroll
+        for (int e = 0; e < U; ++e) {
+          int up = ks[e] < k[e] ? h : 0;
+          if (ks[e] == k[e]) up = (int)sid[bq[e] + h] <= i0 + (q + e) * THREADS ? h : 0;
+          bq[e] += up;
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < U; ++e) b[q + e] = bq[e];
+      __builtin_amdgcn_sched_barrier(0);
     }
+  };
+  auto entry_of = [&](unsigned b) -> int { return (int)((table[b >> 1] >> ((b & 1u) * 16u)) & 0xffffu); };
+  auto count = [&](auto sampled_c) {
+    constexpr bool SAMPLED = decltype(sampled_c)::value != 0;
+    auto batch = [&](int k0, auto&& put) {
+      const int i0 = k0 * THREADS + thread();
+      double uk[BATCH];
+      unsigned b[BATCH], old[BATCH];
 #pragma unroll
-    for (int e = 0; e < BATCH; ++e)
-      bs[k0 + e] |= ((old[e] >> ((bs[k0 + e] & 1u) * 16u)) & 0xffffu) << 16;
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  __syncthreads();
-
-  // 3. bucket starts, in place, and the largest bucket
-  {
+      for (int e = 0; e < BATCH; ++e) uk[e] = u_of(k0, e);
+      if constexpr (SAMPLED) {
+        between(uk, i0, b);
+      } else {
+#pragma unroll
+        for (int e = 0; e < BATCH; ++e) b[e] = linear(uk[e]);
+      }
+#pragma unroll
+      for (int e = 0; e < BATCH; ++e) {
+        old[e] = 0u;
+        if ((okm >> (k0 + e)) & 1u) {
+          if constexpr (KEEP) old[e] = atomicAdd(&table[b[e] >> 1], 1u << ((b[e] & 1u) * 16u));
+          else atomicAdd(&table[b[e] >> 1], 1u << ((b[e] & 1u) * 16u));
+        }
+      }
+      put(i0, b, old);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (KEEP) {
+      batch(0, [&](int, const unsigned (&b)[BATCH], const unsigned (&old)[BATCH]) {
+#pragma unroll
+        for (int e = 0; e < BATCH; ++e) bs[e] = b[e] | (((old[e] >> ((b[e] & 1u) * 16u)) & 0xffffu) << 16);
+      });
+    } else if constexpr (SAMPLED) {
+#pragma unroll 1
+      for (int k0 = 0; k0 < PER; k0 += BATCH)
+        batch(k0, [&](int i0, const unsigned (&b)[BATCH], const unsigned (&)[BATCH]) {
+#pragma unroll
+          for (int e = 0; e < BATCH; ++e)
+            if ((okm >> (k0 + e)) & 1u) a.idx[0][tb + i0 + e * THREADS] = (int)b[e];
+        });
+    } else {
+#pragma unroll
+      for (int k0 = 0; k0 < PER; k0 += BATCH)
+        batch(k0, [&](int, const unsigned (&b)[BATCH], const unsigned (&)[BATCH]) {
+#pragma unroll
+          for (int e = 0; e < BATCH; e += 2) bs[(k0 + e) / 2] = b[e] | (b[e + 1] << 16);
+        });
+    }
+    __syncthreads();
+  };
+  // 3. starts or ends, in place, and the largest bucket
+  auto scan = [&]() {
+    const int wpt = nb / 2 / THREADS;                                // words of two counts a thread
     unsigned c[8], sum = 0, big = 0;                                 // counts of up to 16 buckets
     static_assert(W_::buckets(SORT_ONE) / 2 / THREADS <= 8 || THREADS < 1024, "words of counts a thread");
     if (wpt % 4 == 0) {                                              // 16 bytes a lane: few bank conflicts
 #pragma unroll
       for (int w = 0; w < 8; w += 4)
-        if (w < wpt) *reinterpret_cast<uint4*>(c + w) = *reinterpret_cast<const uint4*>(hist + tid * wpt + w);
+        if (w < wpt) *reinterpret_cast<uint4*>(c + w) = *reinterpret_cast<const uint4*>(table + tid * wpt + w);
     } else {
-      c[0] = hist[tid * wpt];
-      c[1] = wpt > 1 ? hist[tid * wpt + 1] : 0u;
+      c[0] = table[tid * wpt];
+      c[1] = wpt > 1 ? table[tid * wpt + 1] : 0u;
     }
 #pragma unroll
     for (int w = 0; w < 8; ++w)
@@ -512,21 +650,38 @@ __global__ void __launch_bounds__(THREADS) k_sort_one(SortArgs a, int shares, in
     for (int w = 0; w < 8; ++w)
       if (w < wpt) {
         const unsigned e0 = at + (c[w] & 0xffffu), e1 = e0 + (c[w] >> 16);
-        c[w] = at | (e0 << 16);
+        c[w] = KEEP ? at | (e0 << 16) : e0 | (e1 << 16);
         at = e1;
       }
     if (wpt % 4 == 0) {
 #pragma unroll
       for (int w = 0; w < 8; w += 4)
-        if (w < wpt) *reinterpret_cast<uint4*>(hist + tid * wpt + w) = *reinterpret_cast<const uint4*>(c + w);
+        if (w < wpt) *reinterpret_cast<uint4*>(table + tid * wpt + w) = *reinterpret_cast<const uint4*>(c + w);
     } else {
-      hist[tid * wpt] = c[0];
-      if (wpt > 1) hist[tid * wpt + 1] = c[1];
+      table[tid * wpt] = c[0];
+      if (wpt > 1) table[tid * wpt + 1] = c[1];
     }
-    if (tid == THREADS - 1) hist[nb / 2] = at;                       // start of bucket nb: nv
+    if (tid == THREADS - 1) table[nb / 2] = at;                      // (after the last bucket: nv)
+    __syncthreads();
+  };
+  const bool equal = kmin == kmax;                                   // all usable u: the order is that of the indices
+  bool sampled = false;
+  if (__builtin_expect(!equal, 1)) {
+    count(ic<0>{});
+    scan();
+    if (__builtin_expect(s_big > (unsigned)SORT_UNEVEN, 0)) {
+      const int i = (int)((unsigned)(tid * B) / (unsigned)THREADS);
+      __syncthreads();                                               // (s_big is read)
+      sort_samples<THREADS>(baseline_key(a, tb, i), i, skey, sid);
+      nb = 2 * THREADS;
+      sampled = true;
+      if (tid == 0) s_big = 0u;
+      for (int w = tid; w <= nb / 2; w += THREADS) table[w] = 0u;
+      __syncthreads();
+      count(ic<1>{});
+      scan();
+    }
   }
-  __syncthreads();
-  auto start_of = [&](unsigned b) -> int { return (int)((hist[b >> 1] >> ((b & 1u) * 16u)) & 0xffffu); };
 
   // 6. the entries at sorted positions [p0, p1), index_at(j) the baseline at
   // position j (p0 - 1 too, for the bounds)
@@ -588,67 +743,132 @@ __global__ void __launch_bounds__(THREADS) k_sort_one(SortArgs a, int shares, in
     }
   }
 
-  if (B > SORT_SHARE && (nv + shares - 1) / shares + 2 * (int)s_big > cap) {
+  if (__builtin_expect(equal, 0)) {
     unsigned short* perm = reinterpret_cast<unsigned short*>(lds_raw);
-    radix_order<THREADS, PER>(a, tb, perm, perm + ((B + 7) & ~7), s_tot, &s_diff);
-    write((int)((long long)nv * g / G), (int)((long long)nv * (g + 1) / G), [&](int j) { return (int)perm[j]; });
-    return;
-  }
-  for (int sh = g; sh < shares; sh += G) {
-    // the share: the buckets after the one that holds position lo - 1, up to
-    // the one that holds hi - 1. The bucket before it (from ps) is kept too, as
-    // the bounds look at the entry before p0: at most a share and two buckets.
-    const int lo = (int)((long long)nv * sh / shares), hi = (int)((long long)nv * (sh + 1) / shares);
-    if (sh != g) __syncthreads();                    // the last share is written
-    if (tid == 0) {
-      s_heavy = 0;
-      if (lo == 0) s_p0 = s_ps = 0;
-      if (hi == 0) s_p1 = 0;
-    }
-    for (int w = tid; w < nb / 2; w += THREADS) {
-      const unsigned h = hist[w];
-      const int st[3] = {(int)(h & 0xffffu), (int)(h >> 16), (int)(hist[w + 1] & 0xffffu)};
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        if (st[e] < lo && lo <= st[e + 1]) { s_ps = st[e]; s_p0 = st[e + 1]; }
-        if (st[e] < hi && hi <= st[e + 1]) s_p1 = st[e + 1];
-      }
+    int* base = reinterpret_cast<int*>(table);                       // usable ones before each 64 baselines
+    static_assert(PER * WAVES <= THREADS, "one count a thread");
+    auto ballot_of = [&](int k) { return __ballot((okm >> k) & 1u); };
+    for (int k = 0; k < PER; ++k) {
+      const unsigned long long usable = ballot_of(k);
+      if (lane == 0) base[k * WAVES + wave] = __popcll(usable);
     }
     __syncthreads();
-    const int p0 = s_p0, p1 = s_p1, ps = s_ps;
+    const unsigned n = tid < PER * WAVES ? (unsigned)base[tid] : 0u;
+    const unsigned before = block_exclusive<THREADS>(n, s_tot);
+    if (tid < PER * WAVES) base[tid] = (int)before;
+    __syncthreads();
+    for (int k = 0; k < PER; ++k) {
+      const unsigned long long usable = ballot_of(k);
+      const int below = __builtin_amdgcn_mbcnt_hi((unsigned)(usable >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)usable, 0u));
+      if ((okm >> k) & 1u) perm[base[k * WAVES + wave] + below] = (unsigned short)(k * THREADS + tid);
+    }
+    __syncthreads();
+    write((int)((unsigned)(nv * g) / (unsigned)G), (int)((unsigned)(nv * (g + 1)) / (unsigned)G), [&](int j) { return (int)perm[j]; });
+    return;
+  }
+  if constexpr (!KEEP) {
+    if (B > SORT_SHARE && (nv + shares - 1) / shares + 2 * (int)s_big > cap) {
+      unsigned short* perm = reinterpret_cast<unsigned short*>(lds_raw);
+      radix_order<THREADS, PER>(a, tb, perm, perm + ((B + 7) & ~7), s_tot, &s_diff);
+      write((int)((unsigned)(nv * g) / (unsigned)G), (int)((unsigned)(nv * (g + 1)) / (unsigned)G), [&](int j) { return (int)perm[j]; });
+      return;
+    }
+  }
+  static_assert(!KEEP || PER * THREADS <= SORT_SHARE, "a short list is one share's worth of LDS");
+  // the shares: the buckets after the one that holds position lo - 1, up to the
+  // one that holds hi - 1. The bucket before it (from ps) is kept too, as the
+  // bounds look at the entry before p0: at most a share and two buckets.
+  auto lo_of = [&](int sh) { return (int)((unsigned)(nv * sh) / (unsigned)shares); };   // (below 2^19)
+  if (tid < shares) {                                // (what no bucket below writes)
+    if (lo_of(tid) == 0) s_p0[tid] = s_ps[tid] = s_b0[tid] = 0;
+    if (lo_of(tid + 1) == 0) s_p1[tid] = s_b1[tid] = 0;
+  }
+  if (tid == 0) s_heavy = 0;
+  for (int sh = g; sh < shares; sh += G) {
+    const int lo = lo_of(sh), hi = lo_of(sh + 1);
+    for (int w = tid; w < nb / 2; w += THREADS) {
+      const unsigned h = table[w];
+      const int lo16 = (int)(h & 0xffffu), hi16 = (int)(h >> 16);
+      const int other = KEEP ? (int)(table[w + 1] & 0xffffu) : w > 0 ? (int)(table[w - 1] >> 16) : 0;
+      const int at[3] = {KEEP ? lo16 : other, KEEP ? hi16 : lo16, KEEP ? other : hi16};
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        if (at[e] < lo && lo <= at[e + 1]) { s_ps[sh] = at[e]; s_p0[sh] = at[e + 1]; s_b0[sh] = 2 * w + e; }
+        if (at[e] < hi && hi <= at[e + 1]) { s_p1[sh] = at[e + 1]; s_b1[sh] = 2 * w + e; }
+      }
+    }
+  }
+  __syncthreads();
+  for (int sh = g; sh < shares; sh += G) {
+    const int p0 = s_p0[sh], p1 = s_p1[sh], ps = s_ps[sh];
+    const unsigned b0 = s_b0[sh], b1 = s_b1[sh];
     if (p1 <= p0) continue;
-    // 4. keys and indices to their buckets (what follows from baseline numbers
-    // and okm is formed again: kept from the steps before, it spills)
-    int i4 = tid;
-    asm volatile("" : "+v"(okm), "+v"(i4));
+    if (sh != g) {
+      __syncthreads();                               // the last share is written
+      if (tid == 0) s_heavy = 0;
+      if (!KEEP && tid == 0 && p0 > 0) {             // the bucket before p0 may have been in it
+        const unsigned h = (b0 & 1u) * 16u;
+        table[b0 >> 1] = (table[b0 >> 1] & ~(0xffffu << h)) | ((unsigned)p0 << h);
+      }
+      __syncthreads();
+    }
+    // 4. keys and indices to their buckets
+    if constexpr (!KEEP) {
+      if (__builtin_expect(sampled, 0)) {                            // (a thread's own stores)
+#pragma unroll
+        for (int k = 0; k < PER; k += 2) {
+          const int i0 = k * THREADS + thread();
+          const unsigned b0k = (okm >> k) & 1u ? (unsigned)a.idx[0][tb + i0] : 0u;
+          const unsigned b1k = (okm >> (k + 1)) & 1u ? (unsigned)a.idx[0][tb + i0 + THREADS] : 0u;
+          bs[k / 2] = b0k | (b1k << 16);
+        }
+      }
+    }
 #pragma unroll
     for (int k0 = 0; k0 < PER; k0 += BATCH) {
-      int st[BATCH];
+      const int i0 = k0 * THREADS + thread();
       double uk[BATCH];
+      unsigned b[BATCH];
+      int at[BATCH];
 #pragma unroll
       for (int e = 0; e < BATCH; ++e) {
-        const int k = k0 + e;
-        st[e] = start_of(bs[k] & 0xffffu);
-        st[e] = ((okm >> k) & 1u) && st[e] >= ps && st[e] < p1 ? st[e] - ps + (int)(bs[k] >> 16) : -1;
-        uk[e] = st[e] >= 0 ? u_of(k, k * THREADS + i4) : 0.0;
+        if constexpr (KEEP) b[e] = bs[e] & 0xffffu;
+        else b[e] = (bs[(k0 + e) / 2] >> (e % 2 * 16)) & 0xffffu;
+      }
+#pragma unroll
+      for (int e = 0; e < BATCH; ++e) {
+        const bool in = ((okm >> (k0 + e)) & 1u) && b[e] >= b0 && b[e] <= b1;
+        at[e] = -1;
+        if constexpr (KEEP) {
+          if (in) at[e] = entry_of(b[e]) - ps + (int)(bs[e] >> 16);
+        } else if (in) {
+          const unsigned h = (b[e] & 1u) * 16u;
+          at[e] = (int)((atomicSub(&table[b[e] >> 1], 1u << h) >> h) & 0xffffu) - 1 - ps;
+        }
+        uk[e] = at[e] >= 0 ? u_of(k0, e) : 0.0;
       }
 #pragma unroll
       for (int e = 0; e < BATCH; ++e)
-        if (st[e] >= 0) {
-          keys[st[e]] = order_key(uk[e]);
-          ids[st[e]] = (unsigned short)((k0 + e) * THREADS + i4);
+        if (at[e] >= 0) {
+          keys[at[e]] = order_key(uk[e]);
+          ids[at[e]] = (unsigned short)(i0 + e * THREADS);
         }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (s_big > (unsigned)SORT_LIGHT)                                // heavy buckets of the share
-      for (int b = tid; b < nb; b += THREADS) {
-        const int st = start_of(b), n = start_of(b + 1u) - st;
-        if (n > SORT_LIGHT && st >= ps && st < p1)
-          s_list[atomicAdd(&s_heavy, 1)] = ((unsigned)(st - ps) << 16) | (unsigned)n;
-      }
     __syncthreads();
-    const int heavy = s_heavy;
-    if (heavy > 0) {
+    // (of the share's buckets the table now holds the starts)
+    auto span_of = [&](unsigned b, int& st, int& en) {
+      st = entry_of(b) - ps;
+      en = min(entry_of(b + 1u), p1) - ps;
+    };
+    if (__builtin_expect(s_big > (unsigned)SORT_LIGHT, 0)) {         // heavy buckets of the share
+      for (unsigned b = b0 + tid; b <= b1; b += THREADS) {
+        int st, en;
+        span_of(b, st, en);
+        if (en - st > SORT_LIGHT) s_list[atomicAdd(&s_heavy, 1)] = ((unsigned)st << 16) | (unsigned)(en - st);
+      }
+      __syncthreads();
+      const int heavy = s_heavy;
       for (int h = wave; h < heavy; h += WAVES) {
         const int st = (int)(s_list[h] >> 16), n = (int)(s_list[h] & 0xffffu);
         if (n <= SORT_WAVE_MAX) sort_pairs(keys + st, ids + st, n, lane, WAVE, [] { wave_sync(); });
@@ -662,8 +882,17 @@ __global__ void __launch_bounds__(THREADS) k_sort_one(SortArgs a, int shares, in
     // 5. rank within the bucket
     for (int p = tid; p < p1 - ps; p += THREADS) {
       const unsigned long long key = keys[p];
-      const unsigned b = bucket_of(key_value(key));
-      const int st = start_of(b) - ps, en = start_of(b + 1u) - ps;
+      unsigned b;
+      if (__builtin_expect(!sampled, 1)) {
+        b = linear(key_value(key));
+      } else {                                                       // the last bucket that starts at or before p
+        b = b0;
+#pragma unroll 1
+        for (unsigned h = THREADS; h > 0; h /= 2)
+          if (b + h <= b1 && entry_of(b + h) - ps <= p) b += h;
+      }
+      int st, en;
+      span_of(b, st, en);
       int at = p;                                                    // heavy buckets are in order already
       if (en - st <= SORT_LIGHT) {
         int same = 0;
@@ -676,7 +905,8 @@ __global__ void __launch_bounds__(THREADS) k_sort_one(SortArgs a, int shares, in
         }
         if (same > 1) {                                              // equal u: by index
           const unsigned short id = ids[p];
-          for (int e = st; e < en; ++e) at += keys[e] == key && ids[e] < id ? 1 : 0;
+#pragma unroll 4
+          for (int e = st; e < en; ++e) at += (int)(keys[e] == key) & (int)(ids[e] < id);
         }
       }
       ord[at] = (unsigned short)p;
