@@ -1949,7 +1949,8 @@ __device__ __forceinline__ int uniform_half(float2* hbuf, const int* hcnt, int l
 // halves; longer columns load them again. COUNT: hcnt counts the entries of
 // every cell; UNI: cells are divided by their counts. occ: this lane's occupied
 // cells (UNI).
-template <int N, bool ROT, bool UNI, bool COUNT, int SLOTS, class Done>
+// ZEROED: the caller has cleared the buffers for the first half.
+template <int N, bool ROT, bool UNI, bool COUNT, bool ZEROED, int SLOTS, class Done>
 __device__ __forceinline__ void grid_halves(const ImgArgs& a, const ColSpan& c, float2* hbuf, int* hcnt, int t, int ch,
                                             double s, int lane, int& kd, int& kc, int& occ, Claim<SLOTS>& cl,
                                             Done&& done) {
@@ -1959,8 +1960,10 @@ __device__ __forceinline__ void grid_halves(const ImgArgs& a, const ColSpan& c, 
   EntryStep e;
   static_for<0, 2>([&](auto hf) {
     constexpr int HF = decltype(hf)::value;
-    zero_half<N, COUNT>(hbuf, hcnt, lane);
-    wave_sync();
+    if (!(ZEROED && HF == 0)) {
+      zero_half<N, COUNT>(hbuf, hcnt, lane);
+      wave_sync();
+    }
     if (one) {
       if (total > 0) {
         if constexpr (HF == 0) {
@@ -1993,7 +1996,7 @@ template <int N, bool ROT, bool UNI, int ZB, int SLOTS>
 __device__ __forceinline__ void grid_col_half(const ImgArgs& a, const ColSpan& c, float2* hbuf, int* hcnt,
                                               HalfIn<N>& in, int t, int ch, double s, int lane, int& kd,
                                               int& kc, int& occ, Claim<SLOTS>& cl) {
-  grid_halves<N, ROT, UNI, UNI>(a, c, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, [&](auto hf) {
+  grid_halves<N, ROT, UNI, UNI, false>(a, c, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, [&](auto hf) {
     half_read<N, HalfIn<N>::R, decltype(hf)::value, ZB>(hbuf, lane, in.v);
     wave_sync();
   });
@@ -2079,25 +2082,35 @@ __global__ void __launch_bounds__((ColsHalf<N, CPW, UNI>::THREADS)) k_grid_cols_
   else body(ic<0>{});
 }
 
-// The gridding call's column kernel (nearest cell, all N columns): a wavefront
-// grids its column one half of the rows at a time, and the workgroup writes each
-// half of its CPW columns, weighted cells and counts, row by row. Half-length
-// buffers leave room for 16 columns (N <= 1024), so that a row of the tile is a
-// whole 128-byte line of the grid; tiles beyond the outermost baseline write
-// zeros without passing through LDS. Bound by the 12 bytes a cell that it
-// writes: 32 images of 1024^2 126 -> 97 us, 4.2 TB/s (146 us with 8 columns).
+// The gridding call's column kernel (nearest cell, all N columns): a wavefront a
+// column, 16 columns a workgroup (N <= 1024), so that a row of the tile is a whole
+// 128-byte line of the grid; tiles beyond the outermost baseline write zeros
+// without passing through LDS. Up to N = 512 the columns lie whole in LDS (32
+// images of 512^2 with 8,128 baselines 62 -> 60 us against two halves in turn, 4
+// with 32,640 at 51 different u 346 -> 251). Beyond, a wavefront grids one half of
+// the rows at a time and the workgroup writes each half. Columns of more than GU x
+// 64 entries are walked once a half; tiles with one of more than LONG take half of
+// their columns at a time instead, whole ones in two buffers each (in half lines:
+// with a few hundred entries a column the halves are faster, 184 against 195 us
+// for 32 images of 1024^2 with 32,640 baselines).
+// Bound by the 12 bytes a cell that it writes: 32 images of 1024^2 126 -> 97 us,
+// 4.2 TB/s (146 us with 8 columns).
 template <int N>
 struct GridWr {
+  static constexpr bool WHOLE = N <= 512;
+  static constexpr int LONG = 8 * GU * WAVE;
   static constexpr int CPW = N <= 8 ? 8 : N <= 1024 ? 16 : N <= 2048 ? 8 : 4, THREADS = CPW * WAVE;
-  static constexpr int STRIDE = padded_len(N / 2);
-  static constexpr int SLOTS = claim_slots(N / 2);
-  static constexpr size_t LDS = (size_t)CPW * (STRIDE * sizeof(float2) + (N / 2) * sizeof(int) + SLOTS * sizeof(unsigned));
+  static constexpr int ROWS = WHOLE ? N : N / 2;             // of a column's buffer
+  static constexpr int STRIDE = padded_len(ROWS);
+  static constexpr int SLOTS = claim_slots(ROWS);
+  static constexpr size_t LDS = (size_t)CPW * (STRIDE * sizeof(float2) + ROWS * sizeof(int) + SLOTS * sizeof(unsigned));
+  static_assert(WHOLE || padded_len(N) <= 2 * STRIDE, "two buffers hold a whole column");
 };
 
 template <int N, bool UNI>
 __global__ void __launch_bounds__(GridWr<N>::THREADS) k_grid_write(ImgArgs a) {
   using G_ = GridWr<N>;
-  constexpr int H = N / 2, CPW = G_::CPW;
+  constexpr int H = N / 2, CPW = G_::CPW, ROWS = G_::ROWS;
   extern __shared__ float4 lds_raw[];
   __shared__ int red[2 * CPW];
   const int L = blockIdx.x;
@@ -2107,7 +2120,7 @@ __global__ void __launch_bounds__(GridWr<N>::THREADS) k_grid_write(ImgArgs a) {
   if (li >= a.nimg) return;                          // padding of the last group of 8 images
   float2* lds = reinterpret_cast<float2*>(lds_raw);
   int* lcnt = reinterpret_cast<int*>(lds + CPW * G_::STRIDE);
-  unsigned* lclaim = reinterpret_cast<unsigned*>(lcnt + CPW * H);
+  unsigned* lclaim = reinterpret_cast<unsigned*>(lcnt + CPW * ROWS);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = threadIdx.x % WAVE;
   const int img = a.img0 + li;
   const int t = img / a.C, ch = img - t * a.C;
@@ -2138,22 +2151,56 @@ __global__ void __launch_bounds__(GridWr<N>::THREADS) k_grid_write(ImgArgs a) {
   const double s = cells_per_metre(a.freq[ch], a.ndx);
   int kd = 0, kc = 0, occ = 0;
   Claim<G_::SLOTS> cl = claim_init<G_::SLOTS>(lclaim + wave * G_::SLOTS, lane);
-  auto write = [&](auto hf) {
-    constexpr int R0 = decltype(hf)::value * H;
+  // rows [r0, r0 + rows) of columns [w0, w0 + cols) of the tile, column w0 + w from buffer w of `stride`
+  auto write = [&](int r0, auto rows, int w0, auto cols, int stride) {
+    constexpr int RW = decltype(rows)::value, CW = decltype(cols)::value;
     __syncthreads();
-    for (int e = threadIdx.x; e < H * CPW; e += G_::THREADS) {
-      const int r = e / CPW, w = e % CPW;
-      if (w < ncol) {
-        g[(size_t)(R0 + r) * N + w] = lds[w * G_::STRIDE + pad(r)];
-        if (gc) gc[(size_t)(R0 + r) * N + w] = lcnt[w * H + r];
+    for (int e = threadIdx.x; e < RW * CW; e += G_::THREADS) {
+      const int r = e / CW, w = e % CW;
+      if (w0 + w < ncol) {
+        g[(size_t)(r0 + r) * N + w0 + w] = lds[w * stride + pad(r)];
+        if (gc) gc[(size_t)(r0 + r) * N + w0 + w] = lcnt[w * RW + r];
       }
     }
     __syncthreads();
   };
-  float2* hbuf = lds + wave * G_::STRIDE;
-  int* hcnt = lcnt + wave * H;
-  if (a.sd != nullptr) grid_halves<N, true, UNI, true>(a, span, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, write);
-  else grid_halves<N, false, UNI, true>(a, span, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, write);
+  auto whole = [&](float2* buf, int* cnt) {                  // the wavefront's column, all rows
+    for (int r = lane; r < padded_len(N); r += WAVE) buf[r] = make_float2(0.f, 0.f);
+    for (int r = lane; r < N; r += WAVE) cnt[r] = 0;
+    wave_sync();
+    grid_steps<N, true>(a, span, 0, buf, cnt, t, ch, s, lane, kd, kc, cl);
+    wave_sync();
+    if (UNI) occ += uniform_half<2 * N>(buf, cnt, lane);     // (all N rows)
+  };
+  if constexpr (G_::WHOLE) {
+    whole(lds + wave * G_::STRIDE, lcnt + wave * N);
+    write(0, ic<N>{}, 0, ic<CPW>{}, G_::STRIDE);
+  } else {
+    // the first half's buffers are cleared while the bounds arrive; every wavefront
+    // asks for all columns of the tile, so that they agree without a barrier
+    float2* hbuf = lds + wave * G_::STRIDE;
+    int* hcnt = lcnt + wave * H;
+    zero_half<N, true>(hbuf, hcnt, lane);
+    wave_sync();
+    int longest = 0;
+    if (lane < CPW && c0 + lane < N && c0 + lane != H) {
+      const int c = c0 + lane < H ? c0 + lane : c0 + lane - N;
+      const int* bnd = a.bnd + (size_t)img * (N + 2);
+      longest = bnd[c + 1 + H] - bnd[c + H] + bnd[-c + 1 + H] - bnd[-c + H];
+    }
+    if (__ballot(longest > G_::LONG) != 0ull) {
+      constexpr int HC = CPW / 2;
+      __syncthreads();                                         // (all buffers are cleared)
+      for (int part = 0; part < 2; ++part) {
+        if (wave / HC == part) whole(lds + wave % HC * 2 * G_::STRIDE, lcnt + wave % HC * N);
+        write(0, ic<N>{}, part * HC, ic<HC>{}, 2 * G_::STRIDE);
+      }
+    } else {
+      auto half = [&](auto hf) { write(decltype(hf)::value * H, ic<H>{}, 0, ic<CPW>{}, G_::STRIDE); };
+      if (a.sd != nullptr) grid_halves<N, true, UNI, true, true>(a, span, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, half);
+      else grid_halves<N, false, UNI, true, true>(a, span, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, half);
+    }
+  }
   for (int o = WAVE / 2; o > 0; o >>= 1) occ += __shfl_xor(occ, o);
   // baselines are counted once: the direct entry of every column
   if (lane == 0) { red[wave] = UNI ? occ : kd + kc; red[CPW + wave] = kd; }
