@@ -3421,9 +3421,8 @@ __global__ void __launch_bounds__(Cols<N>::THREADS) k_cols_adj(ImgArgs a) {
 // The gradient of one gridded baseline from the column gradient g at its cell:
 // the conjugate of the rotation / cable factor, then vis_grad = conj(g1 conj g2)
 // gamma' and, with gains, gq = gamma' conj(V).
-__device__ __forceinline__ void put_vis_grad(const ImgArgs& a, int li, int img, int ch, size_t tb, int j, float2 g) {
+__device__ __forceinline__ void put_vis_grad(const ImgArgs& a, int li, int img, int ch, size_t tb, int j, int b, float2 g) {
   const size_t vb = (size_t)img * a.B;
-  const int b = a.perm[tb + j];
   if (a.sd != nullptr) g = rotate_phase(g, -a.sd[tb + j], a.freq[ch]);
   if (a.gains) {
     a.vis_grad[vb + b] = cmul(cconj(baseline_gain(a, b)), g);
@@ -3558,8 +3557,15 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_adj_half(ImgArgs 
 // entries (the usual case) keep their rows in registers for both. The u = 0
 // column adds each entry's two rows, which lie in different halves: its lower
 // half waits in registers (`low`, one value per kept entry) or, for longer
-// columns, in the entry's vis_grad slot.
+// columns, in the entry's vis_grad slot. What binds a long column is one wavefront's
+// chain of loads, so those of the next ADJ_AHEAD x 64 entries stay in flight: 2,016
+// baselines in the u = 0 column of 16 images of 512^2 take 82 us with loads as they
+// are needed, 73 two steps ahead and 70 four ahead; 8,128 baselines with half of them
+// in 2% of the u range 90, 82 and 79. (Loaded four at a time and then stored, 92: the
+// next loads wait for the stores.) At N = 1024 four ahead would take more than the
+// 80 registers that let three workgroups share a CU.
 constexpr int GADJ = 4;
+template <int N> constexpr int ADJ_AHEAD = N == 1024 ? 3 : 4;
 
 // The twiddle table is the full one, every power rounded once from 64 bits. Formed
 // from the compact one, w^2k and w^3k carry the rounding of one and two FP32
@@ -3620,18 +3626,17 @@ __global__ void __launch_bounds__((ColsAdj<N, CPW, UNI>::THREADS)) k_cols_adj_ha
   const int nd = c.nd(), total = cs == 0 ? nd : c.total();   // u = 0: its mirror column is itself
   // entry i of the column: its sorted position and its row (N when not kept);
   // mirrored entries take their own row's mirror
+  auto place = [&](int i) { return i >= nd ? c.clo + (i - nd) : c.dlo + i; };
+  auto row_at = [&](int i, double sv) {
+    const double iv = rint(sv * s);
+    if (!(fabs(iv) < (double)H)) return N;
+    int r = (int)iv;
+    if (i >= nd) r = -r;
+    return r < 0 ? r + N : r;
+  };
   auto entry = [&](int i, int& j, int& row) {
-    const bool cj = i >= nd;
-    j = cj ? c.clo + (i - nd) : c.dlo + i;
-    row = N;
-    if (i < total) {
-      const double iv = rint(a.sv[tb + j] * s);
-      if (fabs(iv) < (double)H) {
-        int r = (int)iv;
-        if (cj) r = -r;
-        row = r < 0 ? r + N : r;
-      }
-    }
+    j = place(i);
+    row = i < total ? row_at(i, a.sv[tb + j]) : N;
   };
   int rows[GADJ], js[GADJ];
 #pragma unroll
@@ -3644,17 +3649,16 @@ __global__ void __launch_bounds__((ColsAdj<N, CPW, UNI>::THREADS)) k_cols_adj_ha
     if (UNI) {                                        // cell counts of this half
       for (int r = lane; r < H; r += WAVE) cnt[r] = 0;
       wave_sync();
-      for (int i0 = 0; i0 < c.total(); i0 += WAVE) {
-        const int i = i0 + lane;
-        const bool cj = i >= nd;
-        const int j = cj ? c.clo + (i - nd) : c.dlo + i;
-        if (i < c.total()) {
-          const double iv = rint(a.sv[tb + j] * s);
-          if (fabs(iv) < (double)H) {
-            int r = (int)iv;
-            if (cj) r = -r;
-            r = r < 0 ? r + N : r;
-            if ((r >= H) == (HF == 1)) atomicAdd(&cnt[r - HF * H], 1);
+      for (int i0 = 0; i0 < c.total(); i0 += GADJ * WAVE) {   // (loads of GADJ x 64 entries in flight)
+        double sv[GADJ];
+#pragma unroll
+        for (int u = 0; u < GADJ; ++u) sv[u] = a.sv[tb + place(min(i0 + u * WAVE + lane, c.total() - 1))];
+#pragma unroll
+        for (int u = 0; u < GADJ; ++u) {
+          const int i = i0 + u * WAVE + lane;
+          if (i < c.total()) {
+            const int r = row_at(i, sv[u]);
+            if (r != N && (r >= H) == (HF == 1)) atomicAdd(&cnt[r - HF * H], 1);
           }
         }
       }
@@ -3688,25 +3692,44 @@ __global__ void __launch_bounds__((ColsAdj<N, CPW, UNI>::THREADS)) k_cols_adj_ha
       const int i = u * WAVE + lane;
       if (cs == 0) {                                  // both halves contribute: written after the second
         part(i, rows[u], low[u]);
-        if (HF == 1 && rows[u] != N) put_vis_grad(a, li, img, ch, tb, js[u], low[u]);
+        if (HF == 1 && rows[u] != N) put_vis_grad(a, li, img, ch, tb, js[u], a.perm[tb + js[u]], low[u]);
       } else {
         float2 g = make_float2(0.f, 0.f);
-        if (part(i, rows[u], g)) put_vis_grad(a, li, img, ch, tb, js[u], g);
+        if (part(i, rows[u], g)) put_vis_grad(a, li, img, ch, tb, js[u], a.perm[tb + js[u]], g);
       }
     }
-    for (int i0 = GADJ * WAVE; i0 < total; i0 += WAVE) {
-      int j, row;
-      entry(i0 + lane, j, row);
-      if (row == N) continue;
-      float2 g = make_float2(0.f, 0.f);
-      if (cs == 0) {
-        float2* keep = a.vis_grad + (size_t)img * a.B + a.perm[tb + j];
-        if (HF == 1) g = *keep;
-        part(i0 + lane, row, g);
-        if (HF == 0) *keep = g;
-        else put_vis_grad(a, li, img, ch, tb, j, g);
-      } else if (part(i0 + lane, row, g)) {
-        put_vis_grad(a, li, img, ch, tb, j, g);
+    // longer columns: the loads of the next ADJ_AHEAD x 64 entries are in flight, so that a
+    // step waits neither for its own loads nor for the stores just before it
+    if (total > GADJ * WAVE) {
+      double sv[ADJ_AHEAD<N>];
+      int b[ADJ_AHEAD<N>];
+      auto fetch = [&](int i, int u) {
+        const size_t q = tb + place(min(i, total - 1));
+        sv[u] = a.sv[q];
+        b[u] = a.perm[q];
+      };
+#pragma unroll
+      for (int u = 0; u < ADJ_AHEAD<N>; ++u) fetch((GADJ + u) * WAVE + lane, u);
+#pragma unroll 1
+      for (int i0 = GADJ * WAVE; i0 < total; i0 += ADJ_AHEAD<N> * WAVE) {
+#pragma unroll
+        for (int u = 0; u < ADJ_AHEAD<N>; ++u) {
+          if (i0 + u * WAVE >= total) break;
+          const int i = i0 + u * WAVE + lane, bu = b[u];
+          const int row = i < total ? row_at(i, sv[u]) : N;
+          fetch(i + ADJ_AHEAD<N> * WAVE, u);
+          if (row == N) continue;
+          float2 g = make_float2(0.f, 0.f);
+          if (cs == 0) {
+            float2* keep = a.vis_grad + (size_t)img * a.B + bu;
+            if (HF == 1) g = *keep;
+            part(i, row, g);
+            if (HF == 0) *keep = g;
+            else put_vis_grad(a, li, img, ch, tb, place(i), bu, g);
+          } else if (part(i, row, g)) {
+            put_vis_grad(a, li, img, ch, tb, place(i), bu, g);
+          }
+        }
       }
     }
   };
