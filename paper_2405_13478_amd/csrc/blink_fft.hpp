@@ -479,7 +479,9 @@ __host__ __device__ constexpr bool plan_even(int n) {
 
 // Twiddle and DFT of the butterflies held in registers (no LDS traffic).
 // L: lanes that share a vector (64 / L vectors a wavefront, `lane` within the L).
-template <int N, int R, int NS, int SIGN, int ZB = 0, bool CL = false, int L = WAVE>
+// TIGHT: with the table in memory, one butterfly's last twiddles in flight at a
+// time: loaded early, all of them spill registers where only 128 are at hand.
+template <int N, int R, int NS, int SIGN, int ZB = 0, bool CL = false, int L = WAVE, bool TIGHT = false>
 __device__ __forceinline__ void stage_compute(int lane, const float2* __restrict__ tw,
                                               float2 (&v)[(N / R + L - 1) / L][R]) {
   static_assert(ZB == 0 || NS == 1, "a zero band only on the first stage's inputs");
@@ -487,7 +489,8 @@ __device__ __forceinline__ void stage_compute(int lane, const float2* __restrict
   constexpr int PER = (NB + L - 1) / L;
 #pragma unroll
   for (int p = 0; p < PER; ++p) {
-    const int j = lane + p * L;
+    int j = lane + p * L;
+    if constexpr (TIGHT && NS > 1 && NS * R == N) asm volatile("" : "+v"(j));
     if (NB % L == 0 || j < NB) {
       if constexpr (NS > 1) {
         constexpr int TW0 = tw_entries_before(N, NS);
@@ -510,6 +513,7 @@ __device__ __forceinline__ void stage_compute(int lane, const float2* __restrict
       }
       dft<R, SIGN, ZB>(v[p]);
     }
+    if constexpr (TIGHT && NS > 1) __builtin_amdgcn_sched_barrier(0);
   }
 }
 
@@ -588,13 +592,13 @@ __host__ __device__ constexpr int zero_band(int n, int bound) {
 // its outputs to emit(ic<QB>, X) as stockham_last_emit does.
 // ZB: zero band of the first stage's inputs (NS = 1 only; see zero_band).
 // CL: the table is compact in its last stage (tw_entries_compact).
-template <int N, int SIGN, int NS, int ZB = 0, bool CL = false, int L = WAVE, class Emit>
+template <int N, int SIGN, int NS, int ZB = 0, bool CL = false, int L = WAVE, bool TIGHT = false, class Emit>
 __device__ __forceinline__ void half_chain(float2* hbuf, int lane, const float2* __restrict__ tw,
                                            float2 (&v)[(N / pick_radix(N / NS) + L - 1) / L][pick_radix(N / NS)],
                                            Emit&& emit) {
   constexpr int R = pick_radix(N / NS);
   constexpr int PER = (N / R + L - 1) / L;
-  stage_compute<N, R, NS, SIGN, ZB, CL, L>(lane, tw, v);
+  stage_compute<N, R, NS, SIGN, ZB, CL, L, TIGHT>(lane, tw, v);
   if constexpr (NS * R == N) {
     static_for<0, PER>([&](auto pc) {
       constexpr int p = decltype(pc)::value;
@@ -616,7 +620,7 @@ __device__ __forceinline__ void half_chain(float2* hbuf, int lane, const float2*
     wave_sync();
     half_read<N, R2, 1, 0, L>(hbuf, lane, v2);
     wave_sync();
-    half_chain<N, SIGN, NS * R, 0, CL, L>(hbuf, lane, tw, v2, emit);
+    half_chain<N, SIGN, NS * R, 0, CL, L, TIGHT>(hbuf, lane, tw, v2, emit);
   }
 }
 
@@ -630,11 +634,11 @@ struct HalfIn {
 
 // ZB: the zero band of the first stage's inputs (see zero_band; the inputs in
 // it need not have been read into `in`), 0 for none.
-template <int N, int SIGN, int ZB = 0, bool CL = false, int L = WAVE, class Emit>
+template <int N, int SIGN, int ZB = 0, bool CL = false, int L = WAVE, bool TIGHT = false, class Emit>
 __device__ __forceinline__ void wave_fft_half_emit(float2* hbuf, int lane, const float2* __restrict__ tw,
                                                    HalfIn<N, L>& in, Emit&& emit) {
   static_assert(plan_even(N), "half-length exchange needs even radices");
-  half_chain<N, SIGN, 1, ZB, CL, L>(hbuf, lane, tw, in.v, emit);
+  half_chain<N, SIGN, 1, ZB, CL, L, TIGHT>(hbuf, lane, tw, in.v, emit);
 }
 
 template <int N, int SIGN, int NS = 1>

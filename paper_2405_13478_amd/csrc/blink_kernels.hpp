@@ -2383,6 +2383,15 @@ struct RowsHalf {
   static constexpr size_t LDS = (size_t)(PPW * STRIDE + TW) * sizeof(float2);
 };
 
+// threadIdx.x of a workgroup of whole wavefronts, formed anew from the wavefront's
+// number (in a scalar register) where it is asked for, so that no vector register
+// keeps it.
+__device__ __forceinline__ int thread_number(int wave) {
+  int seed = 0;
+  asm volatile("" : "+s"(seed));
+  return wave * WAVE + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (unsigned)seed));
+}
+
 // HMC > 0: the cutout half-width fixed at compile time (see k_grid_cols_half).
 template <int N, bool AL, bool KB, int HMC = 0>
 __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
@@ -2398,7 +2407,7 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
   static_assert(H % L == 0 && THR == PPW * L, "a tile's slice is whole columns");
   constexpr int R0 = HalfIn<N, L>::R;
   float2* lds = reinterpret_cast<float2*>(lds_raw);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = threadIdx.x % L;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
   const int M = HMC > 0 ? 2 * HMC : a.M;
   const int npair = M / 2;
   const int ntr = (npair + PPW - 1) / PPW;           // row tiles per image
@@ -2412,8 +2421,7 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
     // lane-dependent addresses are formed inside the loop: hoisted out of it
     // they would stay live across the transforms and cost occupancy
-    int lane_i = lane, ln = threadIdx.x;
-    asm volatile("" : "+v"(lane_i), "+v"(ln));
+    const int ln = thread_number(wave), lane_i = ln % L;
     const int vec = L == WAVE ? wave : ln / L;       // this lane's row pair of the tile
     // thread t serves pair slot t % PPW and columns t / PPW + i L; the masks tell
     // the compiler the ranges, so that only i = 0 is ever column 0, and the slots
@@ -2449,7 +2457,7 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
       // a gridding kernel), split over the workgroup and combined in LDS
       int wli = 0;
       float wlf = 0.f;
-      for (int i = ln; i < a.wtiles; i += THR) {
+      for (int i = thread_number(wave); i < a.wtiles; i += THR) {
         const int pv = a.wpart[(size_t)img * a.wstride + i];
         wli += pv;
         wlf += __int_as_float(pv);
@@ -2462,7 +2470,7 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
       float2* z = lds + vec * ST;                       // the packed row its lanes transform
       HalfIn<N, L> in;
       __syncthreads();                                  // previous tile's rows have left LDS
-      if (ln % WAVE == 0) wred[wave] = KB ? __float_as_int(wlf) : wli;
+      if (thread_number(wave) % WAVE == 0) wred[wave] = KB ? __float_as_int(wlf) : wli;
 #pragma unroll
       for (int i = 0; i < EPT; ++i) {                   // lower half: z[k] = A[k] + i B[k]
         const float4 v = ab[i];
@@ -2480,7 +2488,7 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
         W = (float)n;
       }
       const float scale = a.norm ? (W > 0 ? 1.0f / W : 0.0f) : 1.0f;
-      if (p0 == 0 && ln == 0 && a.weight_sum) a.weight_sum[img] = W;
+      if (p0 == 0 && thread_number(wave) == 0 && a.weight_sum) a.weight_sum[img] = W;
       half_read<N, R0, 0, ZB, L>(z, lane_i, in.v);
       __syncthreads();
 #pragma unroll
@@ -2500,12 +2508,16 @@ __global__ void __launch_bounds__(RowsHalf<N>::THREADS) k_rows_half(ImgArgs a) {
           s0 *= lcorr[2 * pair];
           s1 *= lcorr[2 * pair + 1];
         }
+        if constexpr (L == WAVE) {                      // one pair a wavefront: scalars
+          s0 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s0)));
+          s1 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(s1)));
+        }
         int hm = HMC > 0 ? HMC : M / 2;
         // block tests stay inside the loop (hoisted they spill)
         if constexpr (HMC == 0) asm volatile("" : "+s"(hm));
         // image columns of the cutout straight from the last stage: column l
         // holds u-frequency q = (l - M/2) mod N; row 2p is Re z, row 2p+1 is Im z
-        wave_fft_half_emit<N, +1, ZB, false, L>(z, lane_i, tw, in, [&](auto qb, float2 v) {
+        wave_fft_half_emit<N, +1, ZB, false, L, (N > 1024)>(z, lane_i, tw, in, [&](auto qb, float2 v) {
           auto st = [&](unsigned l) {
             const float cl = KB ? lcorr[l] : 1.0f;
             store_at(r0, l, v.x * s0 * cl);
@@ -3144,11 +3156,13 @@ __global__ void __launch_bounds__(FftHalf<N>::CWAVES * WAVE) k_fft_cols_half(flo
     }
   };
   auto store = [&](int half) {
+    int at = r0 * (N / 2) + q;
+    asm volatile("" : "+v"(at));                             // (formed again: kept from the loads, addresses spill at 2048)
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
       const float2* s = lds + 2 * q * ST + pad(r0 + e * ROWS);
       const float2 a = s[0], b = s[ST];
-      img[(size_t)(half * H + r0 + e * ROWS) * (N / 2) + q] = make_float4(a.x, a.y, b.x, b.y);
+      store_at(img + (size_t)(half * H + e * ROWS) * (N / 2), (unsigned)at, make_float4(a.x, a.y, b.x, b.y));
     }
   };
   const float2* tw = stage_twiddles<N>(lds + CPW * ST);
