@@ -1479,6 +1479,12 @@ __device__ __forceinline__ void kb_add_rows(float2* buf, int* cnt, int j0, int n
     constexpr int BITS = N >= 1024 ? 10 : N >= 512 ? 9 : N >= 256 ? 8 : 7;
     const int below = rank_among_equal<BITS>(j0, active);
     const int rank = active ? below : -1;
+    float wl = 0.f;                                    // w[kw]
+#pragma unroll
+    for (int k = 0; k <= KMAX; ++k) {
+      if (k > kw) break;
+      wl = w[k];
+    }
     for (int t = 0; __ballot(rank >= t) != 0; ++t) {
       if (rank == t) {
 #pragma unroll
@@ -1490,10 +1496,6 @@ __device__ __forceinline__ void kb_add_rows(float2* buf, int* cnt, int j0, int n
           wave_sync();
         }
         if (nrow > kw) {                               // the few footprints of W + 1 rows
-          float wl = 0.f;
-#pragma unroll
-          for (int k = 0; k <= KMAX; ++k)
-            if (k == kw) wl = w[k];
           const float2 d = row[kw];
           row[kw] = make_float2(d.x + wl * v.x, d.y + wl * v.y);
           if (COUNT) cnt[j0 + N / 2 + kw] += 1;
