@@ -1951,8 +1951,7 @@ __device__ __forceinline__ int uniform_half(float2* hbuf, const int* hcnt, int l
 // halves; longer columns load them again. COUNT: hcnt counts the entries of
 // every cell; UNI: cells are divided by their counts. occ: this lane's occupied
 // cells (UNI).
-// ZEROED: the caller has cleared the buffers for the first half.
-template <int N, bool ROT, bool UNI, bool COUNT, bool ZEROED, int SLOTS, class Done>
+template <int N, bool ROT, bool UNI, bool COUNT, int SLOTS, class Done>
 __device__ __forceinline__ void grid_halves(const ImgArgs& a, const ColSpan& c, float2* hbuf, int* hcnt, int t, int ch,
                                             double s, int lane, int& kd, int& kc, int& occ, Claim<SLOTS>& cl,
                                             Done&& done) {
@@ -1962,10 +1961,8 @@ __device__ __forceinline__ void grid_halves(const ImgArgs& a, const ColSpan& c, 
   EntryStep e;
   static_for<0, 2>([&](auto hf) {
     constexpr int HF = decltype(hf)::value;
-    if (!(ZEROED && HF == 0)) {
-      zero_half<N, COUNT>(hbuf, hcnt, lane);
-      wave_sync();
-    }
+    zero_half<N, COUNT>(hbuf, hcnt, lane);
+    wave_sync();
     if (one) {
       if (total > 0) {
         if constexpr (HF == 0) {
@@ -1998,7 +1995,7 @@ template <int N, bool ROT, bool UNI, int ZB, int SLOTS>
 __device__ __forceinline__ void grid_col_half(const ImgArgs& a, const ColSpan& c, float2* hbuf, int* hcnt,
                                               HalfIn<N>& in, int t, int ch, double s, int lane, int& kd,
                                               int& kc, int& occ, Claim<SLOTS>& cl) {
-  grid_halves<N, ROT, UNI, UNI, false>(a, c, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, [&](auto hf) {
+  grid_halves<N, ROT, UNI, UNI>(a, c, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, [&](auto hf) {
     half_read<N, HalfIn<N>::R, decltype(hf)::value, ZB>(hbuf, lane, in.v);
     wave_sync();
   });
@@ -2178,29 +2175,30 @@ __global__ void __launch_bounds__(GridWr<N>::THREADS) k_grid_write(ImgArgs a) {
     whole(lds + wave * G_::STRIDE, lcnt + wave * N);
     write(0, ic<N>{}, 0, ic<CPW>{}, G_::STRIDE);
   } else {
-    // the first half's buffers are cleared while the bounds arrive; every wavefront
-    // asks for all columns of the tile, so that they agree without a barrier
+    // every wavefront asks for the tile's entries and, where they are many, for those
+    // of all its columns, so that they agree without a barrier
+    static_assert(H % CPW == 0, "a tile lies on one side of column N / 2");
     float2* hbuf = lds + wave * G_::STRIDE;
     int* hcnt = lcnt + wave * H;
-    zero_half<N, true>(hbuf, hcnt, lane);
-    wave_sync();
-    int longest = 0;
-    if (lane < CPW && c0 + lane < N && c0 + lane != H) {
-      const int c = c0 + lane < H ? c0 + lane : c0 + lane - N;
-      const int* bnd = a.bnd + (size_t)img * (N + 2);
-      longest = bnd[c + 1 + H] - bnd[c + H] + bnd[-c + 1 + H] - bnd[-c + H];
+    const int* bnd = a.bnd + (size_t)img * (N + 2);
+    const int u0 = c0 < H ? c0 : c0 - N;
+    const int inside = bnd[u0 + CPW + H] - bnd[u0 + H] + bnd[-u0 + 1 + H] - bnd[-u0 - CPW + 1 + H];
+    bool few = inside <= G_::LONG;
+    if (!few) {
+      const int c = u0 + lane;
+      few = __ballot(lane < CPW && c != -H &&
+                     bnd[c + 1 + H] - bnd[c + H] + bnd[-c + 1 + H] - bnd[-c + H] > G_::LONG) == 0ull;
     }
-    if (__ballot(longest > G_::LONG) != 0ull) {
+    if (!few) {
       constexpr int HC = CPW / 2;
-      __syncthreads();                                         // (all buffers are cleared)
       for (int part = 0; part < 2; ++part) {
         if (wave / HC == part) whole(lds + wave % HC * 2 * G_::STRIDE, lcnt + wave % HC * N);
         write(0, ic<N>{}, part * HC, ic<HC>{}, 2 * G_::STRIDE);
       }
     } else {
       auto half = [&](auto hf) { write(decltype(hf)::value * H, ic<H>{}, 0, ic<CPW>{}, G_::STRIDE); };
-      if (a.sd != nullptr) grid_halves<N, true, UNI, true, true>(a, span, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, half);
-      else grid_halves<N, false, UNI, true, true>(a, span, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, half);
+      if (a.sd != nullptr) grid_halves<N, true, UNI, true>(a, span, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, half);
+      else grid_halves<N, false, UNI, true>(a, span, hbuf, hcnt, t, ch, s, lane, kd, kc, occ, cl, half);
     }
   }
   for (int o = WAVE / 2; o > 0; o >>= 1) occ += __shfl_xor(occ, o);
