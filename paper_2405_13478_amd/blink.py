@@ -116,10 +116,9 @@ def supported_n(n: int) -> bool:
 
 
 # ---------------------------------------------------------------- helpers
-# A small image takes the GPU about 20 us, so what the binding does per call
-# counts: addresses go as plain ints (ctypes converts them), the checks avoid
-# building device and size objects, and the current stream is asked for by
-# number: 29.5 -> 24 us per 128^2 image, back to back.
+# A small image keeps the GPU busy for about as long as the binding takes to
+# launch it, so addresses go as plain ints (ctypes converts them), the checks
+# build no device and size objects, and the current stream is asked for by number.
 def _ptr(t):
     return None if t is None else t.data_ptr()
 

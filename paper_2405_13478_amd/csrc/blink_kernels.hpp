@@ -1462,8 +1462,9 @@ __device__ __forceinline__ int rank_among_equal(int key, bool active) {
 // different j0 never reach the same row at the same k, so a turn adds all of its
 // lanes' rows in sequence over k. Each element receives its adds in a fixed
 // order: step, turn, k. In the signed layout a lane's turn is the number of lanes
-// below it with the same j0, from ballots (no LDS round trips before a turn, and
-// no waiting for lanes whose j0 only shares a claim slot); the other sizes claim
+// below it with the same j0 (at N = 2048 the same j0 mod 1024, so that rows 1024
+// apart take turns too), from ballots (no LDS round trips before a turn, and no
+// waiting for lanes whose j0 only shares a claim slot); the other sizes claim
 // turns as wave_add does, keyed on j0. nrow is W or W + 1; in the signed layout the
 // few lanes with W + 1 add the last one apart (added to all with weight 0, it would
 // spread an infinite or NaN visibility to the row after the footprint).
@@ -1748,6 +1749,9 @@ __global__ void __launch_bounds__((Cols<N, CPW>::THREADS)) k_grid_cols(ImgArgs a
   if (CNT)
     for (int r = lane; r < N; r += WAVE) cnt[r] = 0;
   unsigned* lclaim = reinterpret_cast<unsigned*>(lcnt + (CNT ? CPW * N : 0));
+  // (the signed rows of kernel gridding take their turns from ballots; leaving out their
+  // slots was slower: 24 images of 512^2, 6-cell kernel, half of 4,950 baselines in 2% of
+  // the u range 630 -> 655 us, none faster)
   Claim<C_::SLOTS> cl = claim_init<C_::SLOTS>(lclaim + wave * C_::SLOTS, lane);
   wave_sync();
 
@@ -2724,8 +2728,8 @@ struct Xe {
   static constexpr size_t LDS = RING * (size_t)BUF * 16;      // 64 KiB: the reach of a load's LDS offset
   static_assert(VPT * RING <= 16 && LDS <= 65536, "xe_wait counts up to 12 loads");
   // place of unit c of row r, and the unit at place c (the same permutation):
-  // a row covers a quarter (64 bytes) or half (128) of the banks
-  __device__ static int unit(int r, int c) { return r * UNITS + (c ^ (CH == 64 ? (r >> 2) & 3 : (r >> 1) & 7)); }
+  // a row covers half of the banks
+  __device__ static int unit(int r, int c) { return r * UNITS + (c ^ ((r >> 1) & 7)); }
 };
 
 // 16 bytes a lane from memory to LDS at byte `at` + 16 lane (wave-uniform
@@ -2894,7 +2898,7 @@ __global__ void __launch_bounds__(XE_THREADS, 2) k_xengine(XeArgs a) {
 // at compile time, so that a wavefront reads its row operand once for several
 // blocks. Double-buffered: the next 256 bytes of every row are in flight in
 // registers during the products of these.
-// 512 spectra of 256 antennas x 4096 samples: 617 -> 375 us (552 TOP of the
+// 512 spectra of 256 antennas x 4096 samples: 617 -> 375 us (0.55 TOP of the
 // definition's 8 operations a pair and sample: 1.5 POP/s; 2.9 TB/s of input),
 // against 617 with one wavefront per 64 x 64 tile on split real and imaginary
 // bytes. With the matrix cores and the loads both busy the clock falls from 2.2
