@@ -32,11 +32,7 @@ def _to(x):
     return torch.from_numpy(np.ascontiguousarray(x)).to(device())
 
 
-@pytest.mark.parametrize("uniform", [0, 1])
-@pytest.mark.parametrize("N", [8, 12, 32, 128, 180, 256, 512, 1024, 2048, 4096])
-def test_uv_grid_of_long_columns(N, uniform):
-    rng = np.random.default_rng(N + uniform)
-    _, _, uvw, flags, vis = _long(N, rng)
+def _check_grid(uvw, flags, vis, N, uniform):
     freq, pix = np.array([oracle.C_LIGHT]), 1.0 / N               # one cell a metre
     g, c, w, d = blink.grid(_to(vis), _to(uvw), _to(freq), grid_n=N, pixscale=pix, weighting=uniform, flags=_to(flags))
     s = oracle.blink_oracle.uv_scale(freq[0], N, pix)
@@ -46,6 +42,26 @@ def test_uv_grid_of_long_columns(N, uniform):
     assert np.array_equal(c.cpu().numpy()[0], cnt)
     assert float(w[0]) == W and int(d[0]) == int(((flags[0] == 0) & ~keep).sum())
     assert rel_l2(g.cpu().numpy()[0].view(np.float32), np.ascontiguousarray(G).view(np.float64)) <= REL_L2_FP32
+
+
+@pytest.mark.parametrize("uniform", [0, 1])
+@pytest.mark.parametrize("N", [8, 12, 32, 128, 180, 256, 512, 1024, 2048, 4096])
+def test_uv_grid_of_long_columns(N, uniform):
+    rng = np.random.default_rng(N + uniform)
+    _, _, uvw, flags, vis = _long(N, rng)
+    _check_grid(uvw, flags, vis, N, uniform)
+
+
+# many entries in a tile of columns, none of which is long: around u = 0, on one
+# side of it and in the last columns that can hold any
+@pytest.mark.parametrize("place,uniform", [("centre", 0), ("side", 1), ("edge", 0)])
+@pytest.mark.parametrize("N", [1024, 2048, 4096])
+def test_uv_grid_of_full_tiles(N, place, uniform):
+    rng = np.random.default_rng(N)
+    _, _, uvw, flags, vis = _long(N, rng)
+    first = {"centre": -8, "side": 40, "edge": N // 2 - 16}[place]
+    uvw[0, :, 0] = first + rng.integers(0, 16, uvw.shape[1])
+    _check_grid(uvw, flags, vis, N, uniform)
 
 
 @pytest.mark.parametrize("N,M,uniform,gains", [(32, 16, 0, True), (64, 64, 1, False), (128, 64, 0, False), (256, 128, 1, True),
